@@ -75,26 +75,6 @@ __global__ __launch_bounds__(256) void kg_row_g(const GroupTask<RowParams>* __re
   const GroupTask<RowParams>& T = group_task(tasks, bt);
   row_g_body<MODE, ST, STATS, RW>(T.p, T.gp, group_block(T));
 }
-__global__ __launch_bounds__(256) void kg_colg_fwd(const GroupTask<ColParams>* __restrict__ tasks,
-                                                  const uint16_t* __restrict__ bt) {
-  const GroupTask<ColParams>& T = group_task(tasks, bt);
-  colg_fwd_body(T.p, T.gp, group_block(T));
-}
-__global__ __launch_bounds__(256) void kg_colg_syn(const GroupTask<ColParams>* __restrict__ tasks,
-                                                  const uint16_t* __restrict__ bt) {
-  const GroupTask<ColParams>& T = group_task(tasks, bt);
-  colg_syn_body(T.p, T.gp, group_block(T));
-}
-__global__ __launch_bounds__(256) void kg_colg_ana(const GroupTask<ColParams>* __restrict__ tasks,
-                                                  const uint16_t* __restrict__ bt) {
-  const GroupTask<ColParams>& T = group_task(tasks, bt);
-  colg_ana_body(T.p, T.gp, group_block(T));
-}
-__global__ __launch_bounds__(256) void kg_colg_final(const GroupTask<ColParams>* __restrict__ tasks,
-                                                    const uint16_t* __restrict__ bt) {
-  const GroupTask<ColParams>& T = group_task(tasks, bt);
-  colg_final_body(T.p, T.gp, group_block(T));
-}
 
 // ---- pixel step (any size)
 template <bool STATS, bool HAVE_Z>

@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256) void k_nl_primal(NlParams p) {
 }
 
 // Energy partials of u: <u, s> and lambda sum_i (sum_{l, b} (D_b u_l)(i)^2)^(1/2), FP64.
-__global__ __launch_bounds__(256) void k_nl_energy(NlParams p) {
+static __global__ __launch_bounds__(256) void k_nl_energy(NlParams p) {
   __shared__ double red[4 * 4];
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};

@@ -14,61 +14,12 @@
 #include <string>
 #include <vector>
 
-#include "shearseg.h"
-#include "kernels.hpp"
-#include "generic.hpp"
-#include "grouped.hpp"
+#include "host.hpp"
+#include "misc.hpp"
 #include "tv.hpp"
 #include "nl.hpp"
 
-using namespace shs;
-
-struct shs_plan {
-  int n, C, q, J, store, eta, M, P, PP, W, NS, device;
-  int generic;         // 1: mixed-radix path (N not a power of two)
-  int rpb;             // rows per row-pass block
-  int rw;              // generic path: rows per wave of the row pass (1, 2 or 4)
-  int wpb;             // generic path: waves per row-pass block (1, 2 or 4)
-  FftPlan prow, pcol;  // mixed-radix stage lists (generic path)
-  float* psi;          // [eta][N][PP] dense filter bank (half spectrum)
-  float2* tw;          // [N] exp(-2 pi i m / N), then (power-of-two N) the FFT stage tables
-  float* eig;          // [N] 4 sin^2(pi k / N): DFT eigenvalues of one forward-difference pair (TV)
-  // pruned layout
-  float* psiw;         // filter values inside each column window
-  int4* pwin;          // [eta][M+1] {a, L, value offset, 0}
-  int4* tcol;          // [eta] {cb, pitch, off_lo, off_hi} of the filtered spectra
-  long long t_ls;      // label stride of the filtered spectra (float2)
-  // column work lists
-  int4* items_syn;     // {strip, flist offset, count, -1}
-  int4* items_ana;     // {strip, flist offset, count, partial slot or -1}
-  int* flist;          // filter ids, grouped by strip
-  int2* strips_ana;    // per strip {first analysis item, items}
-  int n_syn, n_ana, n_part;
-  int fc_syn;          // filters per synthesis work item
-  long long nnz;       // stored filter values
-  struct GraphCache* graphs;  // captured steady-state iterations of shs_solve
-  char schedule[256];  // chosen launch schedule (shs_plan_describe)
-};
-
-// Executable graphs of steady-state ADMM iterations, keyed by everything the captured
-// launches bake in (workspace, data term, history, thresholds, iteration count).  Captured
-// on a stream of the plan's own and launched on the caller's stream; a few entries, least
-// recently used dropped first.  The mutex makes lookups, captures and launches of one plan
-// safe from several host threads.
-struct GraphCache {
-  struct Entry {
-    std::vector<uint64_t> key;
-    hipGraphExec_t exec;
-  };
-  std::mutex mu;
-  hipStream_t cap = nullptr;
-  std::vector<Entry> entries;   // most recently used last
-  static constexpr size_t kMax = 6;
-  ~GraphCache() {
-    for (Entry& e : entries) (void)hipGraphExecDestroy(e.exec);
-    if (cap) (void)hipStreamDestroy(cap);
-  }
-};
+thread_local shs::Recorder* shs::g_rec = nullptr;
 
 namespace {
 
@@ -261,208 +212,6 @@ Layout make_layout(const shs_plan* p) {
   return L;
 }
 
-// ---------------------------------------------------------------- launch recording (batches)
-// While a Recorder is installed (this thread), the launchers below append a description of
-// each launch, with the grouped kernel of its configuration, instead of launching; the
-// batch solve turns one iteration's records of all images into grouped launches.  Each
-// record carries the step of the iteration it belongs to.
-enum BatchStep { BS_ANA, BS_FINAL, BS_C2R, BS_PIXEL, BS_R2C, BS_FWD, BS_SYN, BS_ROW, BS_REDUCE, BS_COUNT };
-enum RecKind { RK_ROW, RK_COL, RK_PIX, RK_REDUCE };
-struct LaunchRec {
-  int step = 0, kind = 0;
-  const void* fn = nullptr;    // grouped kernel of the launch's configuration
-  int threads = 0, gx = 0, gy = 0;
-  size_t lds = 0;              // dynamic LDS bytes
-  RowParams rp{};
-  ColParams cp{};
-  PixParams pp{};
-  GenParams gp{};
-  // RK_REDUCE (one image's two-level FP64 reduction)
-  double* parts = nullptr;
-  long long nparts = 0;
-  double* red1 = nullptr;
-  double* sdev = nullptr;
-  double gamma = 1.0;
-};
-struct Recorder {
-  std::vector<LaunchRec> recs;
-  int step = 0;
-};
-thread_local Recorder* g_rec = nullptr;
-void rec_step(int s) {
-  if (g_rec) g_rec->step = s;
-}
-template <class F>
-LaunchRec& rec_add(int kind, F fn, int threads, int gx, int gy, size_t lds) {
-  LaunchRec r;
-  r.step = g_rec->step;
-  r.kind = kind;
-  r.fn = reinterpret_cast<const void*>(fn);
-  r.threads = threads;
-  r.gx = gx;
-  r.gy = gy;
-  r.lds = lds;
-  g_rec->recs.push_back(r);
-  return g_rec->recs.back();
-}
-
-// ---------------------------------------------------------------- per-size launchers
-template <int N>
-struct Pipe {
-  using RG = RowGeom<N>;
-  using CG = ColCfg<N>;
-
-  template <int MODE, int ST, bool STATS>
-  static void row_t(const RowParams& rp, int channels, hipStream_t s) {
-    dim3 grid(N / RG::RPB, channels);
-    if (g_rec) {
-      rec_add(RK_ROW, &kg_row<N, MODE, ST, STATS>, RG::THREADS, N / RG::RPB, channels, 0).rp = rp;
-      return;
-    }
-    hipLaunchKernelGGL((k_row<N, MODE, ST, STATS>), grid, dim3(RG::THREADS), 0, s, rp);
-  }
-  static void row(const shs_plan*, int mode, int store, bool stats, const RowParams& rp, int channels, hipStream_t s) {
-    switch (mode) {
-      case ROW_SOLVE:
-        if (store == ST_F32) { stats ? row_t<ROW_SOLVE, ST_F32, true>(rp, channels, s) : row_t<ROW_SOLVE, ST_F32, false>(rp, channels, s); }
-        else if (store == ST_BF16) { stats ? row_t<ROW_SOLVE, ST_BF16, true>(rp, channels, s) : row_t<ROW_SOLVE, ST_BF16, false>(rp, channels, s); }
-        else { stats ? row_t<ROW_SOLVE, ST_F16, true>(rp, channels, s) : row_t<ROW_SOLVE, ST_F16, false>(rp, channels, s); }
-        break;
-      case ROW_PRIME:
-        if (store == ST_F32) row_t<ROW_PRIME, ST_F32, false>(rp, channels, s);
-        else if (store == ST_BF16) row_t<ROW_PRIME, ST_BF16, false>(rp, channels, s);
-        else row_t<ROW_PRIME, ST_F16, false>(rp, channels, s);
-        break;
-      case ROW_C2R: row_t<ROW_C2R, ST_F32, false>(rp, channels, s); break;
-      case ROW_R2C: row_t<ROW_R2C, ST_F32, false>(rp, channels, s); break;
-      case ROW_ENERGY: row_t<ROW_ENERGY, ST_F32, true>(rp, channels, s); break;
-      case ROW_SHRINK: row_t<ROW_SHRINK, ST_F32, false>(rp, channels, s); break;
-      case ROW_PD:
-        if (store == ST_F32) { stats ? row_t<ROW_PD, ST_F32, true>(rp, channels, s) : row_t<ROW_PD, ST_F32, false>(rp, channels, s); }
-        else if (store == ST_BF16) { stats ? row_t<ROW_PD, ST_BF16, true>(rp, channels, s) : row_t<ROW_PD, ST_BF16, false>(rp, channels, s); }
-        else { stats ? row_t<ROW_PD, ST_F16, true>(rp, channels, s) : row_t<ROW_PD, ST_F16, false>(rp, channels, s); }
-        break;
-    }
-  }
-  static void col(const shs_plan*, int kind, const ColParams& cp, int nblocks, int labels, hipStream_t s) {
-    const dim3 grid(nblocks, labels), block(CG::THREADS);
-    if (g_rec) {
-      LaunchRec* r = nullptr;
-      switch (kind) {
-        case 0: r = &rec_add(RK_COL, &kg_col_fwd<N>, CG::THREADS, nblocks, labels, 0); break;
-        case 1: r = &rec_add(RK_COL, &kg_col_syn<N>, CG::THREADS, nblocks, labels, 0); break;
-        case 2: r = &rec_add(RK_COL, &kg_col_ana<N>, CG::THREADS, nblocks, labels, 0); break;
-        case 3: r = &rec_add(RK_COL, &kg_col_final<N>, CG::THREADS, nblocks, labels, 0); break;
-      }
-      if (r) r->cp = cp;
-      return;
-    }
-    switch (kind) {
-      case 0: hipLaunchKernelGGL((k_col_fwd<N>), grid, block, 0, s, cp); break;
-      case 1: hipLaunchKernelGGL((k_col_syn<N>), grid, block, 0, s, cp); break;
-      case 2: hipLaunchKernelGGL((k_col_ana<N>), grid, block, 0, s, cp); break;
-      case 3: hipLaunchKernelGGL((k_col_final<N>), grid, block, 0, s, cp); break;
-    }
-  }
-};
-enum { COL_FWD = 0, COL_SYN = 1, COL_ANA = 2, COL_FINAL = 3 };
-
-// Dynamic LDS of a generic row-pass block: two half-length buffers of rw rows per wave,
-// then the twiddle tables.
-size_t row_g_lds_bytes(int M, int rw, int wpb, int n) {
-  return (size_t(wpb) * 2 * M * rw + row_tab_len(n)) * sizeof(float2);
-}
-constexpr size_t kRowGLdsMax = 64 * 1024;   // dynamic LDS a generic row block may take
-
-// Mixed-radix (generic) launchers: runtime N, one row per wave, LDS-resident transforms.
-struct GenPipe {
-  static GenParams gp(const shs_plan* p) { return GenParams{p->prow, p->pcol, p->n, p->wpb}; }
-  template <int MODE, int ST, bool STATS>
-  static void row_t(const shs_plan* p, const RowParams& rp, int channels, hipStream_t s) {
-    // p->wpb waves per block, p->rw rows per wave
-    const dim3 grid(p->n / p->rpb, channels);
-    const int threads = 64 * p->wpb;
-    const size_t lds = row_g_lds_bytes(p->M, p->rw, p->wpb, p->n);
-    if (g_rec) {
-      LaunchRec* r = nullptr;
-      switch (p->rw) {
-        case 4: r = &rec_add(RK_ROW, &kg_row_g<MODE, ST, STATS, 4>, threads, p->n / p->rpb, channels, lds); break;
-        case 2: r = &rec_add(RK_ROW, &kg_row_g<MODE, ST, STATS, 2>, threads, p->n / p->rpb, channels, lds); break;
-        default: r = &rec_add(RK_ROW, &kg_row_g<MODE, ST, STATS, 1>, threads, p->n / p->rpb, channels, lds); break;
-      }
-      r->rp = rp;
-      r->gp = gp(p);
-      return;
-    }
-    switch (p->rw) {
-      case 4: hipLaunchKernelGGL((k_row_g<MODE, ST, STATS, 4>), grid, dim3(threads), lds, s, rp, gp(p)); break;
-      case 2: hipLaunchKernelGGL((k_row_g<MODE, ST, STATS, 2>), grid, dim3(threads), lds, s, rp, gp(p)); break;
-      default: hipLaunchKernelGGL((k_row_g<MODE, ST, STATS, 1>), grid, dim3(threads), lds, s, rp, gp(p)); break;
-    }
-  }
-  static void row(const shs_plan* p, int mode, int store, bool stats, const RowParams& rp, int channels,
-                  hipStream_t s) {
-    switch (mode) {
-      case ROW_SOLVE:
-        if (store == ST_F32) { stats ? row_t<ROW_SOLVE, ST_F32, true>(p, rp, channels, s) : row_t<ROW_SOLVE, ST_F32, false>(p, rp, channels, s); }
-        else if (store == ST_BF16) { stats ? row_t<ROW_SOLVE, ST_BF16, true>(p, rp, channels, s) : row_t<ROW_SOLVE, ST_BF16, false>(p, rp, channels, s); }
-        else { stats ? row_t<ROW_SOLVE, ST_F16, true>(p, rp, channels, s) : row_t<ROW_SOLVE, ST_F16, false>(p, rp, channels, s); }
-        break;
-      case ROW_PRIME:
-        if (store == ST_F32) row_t<ROW_PRIME, ST_F32, false>(p, rp, channels, s);
-        else if (store == ST_BF16) row_t<ROW_PRIME, ST_BF16, false>(p, rp, channels, s);
-        else row_t<ROW_PRIME, ST_F16, false>(p, rp, channels, s);
-        break;
-      case ROW_C2R: row_t<ROW_C2R, ST_F32, false>(p, rp, channels, s); break;
-      case ROW_R2C: row_t<ROW_R2C, ST_F32, false>(p, rp, channels, s); break;
-      case ROW_ENERGY: row_t<ROW_ENERGY, ST_F32, true>(p, rp, channels, s); break;
-      case ROW_SHRINK: row_t<ROW_SHRINK, ST_F32, false>(p, rp, channels, s); break;
-      case ROW_PD:
-        if (store == ST_F32) { stats ? row_t<ROW_PD, ST_F32, true>(p, rp, channels, s) : row_t<ROW_PD, ST_F32, false>(p, rp, channels, s); }
-        else if (store == ST_BF16) { stats ? row_t<ROW_PD, ST_BF16, true>(p, rp, channels, s) : row_t<ROW_PD, ST_BF16, false>(p, rp, channels, s); }
-        else { stats ? row_t<ROW_PD, ST_F16, true>(p, rp, channels, s) : row_t<ROW_PD, ST_F16, false>(p, rp, channels, s); }
-        break;
-    }
-  }
-  static void col(const shs_plan* p, int kind, const ColParams& cp, int nblocks, int labels, hipStream_t s) {
-    const dim3 grid(nblocks, labels), block(256);
-    const size_t e = size_t(p->n) * kGW * sizeof(float2);
-    const size_t t = size_t(col_tab_len(p->n)) * sizeof(float2);
-    if (g_rec) {
-      LaunchRec* r = nullptr;
-      switch (kind) {
-        case 0: r = &rec_add(RK_COL, &kg_colg_fwd, 256, nblocks, labels, t + 2 * e); break;
-        case 1: r = &rec_add(RK_COL, &kg_colg_syn, 256, nblocks, labels, t + 3 * e); break;
-        case 2: r = &rec_add(RK_COL, &kg_colg_ana, 256, nblocks, labels, t + 3 * e); break;
-        case 3: r = &rec_add(RK_COL, &kg_colg_final, 256, nblocks, labels, t + 2 * e); break;
-      }
-      if (r) {
-        r->cp = cp;
-        r->gp = gp(p);
-      }
-      return;
-    }
-    switch (kind) {
-      case 0: hipLaunchKernelGGL(k_colg_fwd, grid, block, t + 2 * e, s, cp, gp(p)); break;
-      case 1: hipLaunchKernelGGL(k_colg_syn, grid, block, t + 3 * e, s, cp, gp(p)); break;
-      case 2: hipLaunchKernelGGL(k_colg_ana, grid, block, t + 3 * e, s, cp, gp(p)); break;
-      case 3: hipLaunchKernelGGL(k_colg_final, grid, block, t + 2 * e, s, cp, gp(p)); break;
-    }
-  }
-};
-
-struct Ops {
-  void (*row)(const shs_plan*, int, int, bool, const RowParams&, int, hipStream_t);
-  void (*col)(const shs_plan*, int, const ColParams&, int, int, hipStream_t);
-};
-
-template <int N>
-Ops ops_for() {
-  return Ops{&Pipe<N>::row, &Pipe<N>::col};
-}
-
-constexpr int kGenericMaxN = 1024;   // largest image side of the mixed-radix path
-
 // Stage list of a mixed-radix transform of length L (radices 16, 8, 4, 2, 9, 3 and the
 // primes 5..23); false if L has a larger prime factor.
 // Default stage list of length L: empty if L has a prime factor above 23.
@@ -505,18 +254,18 @@ bool make_fft_plan(int L, FftPlan& pl) { return fft_plan_from(L, fft_factors(L),
 bool get_ops_pow2(int n, Ops& o);
 
 bool get_ops(const shs_plan* p, Ops& o) {
-  if (p->generic) { o = Ops{&GenPipe::row, &GenPipe::col}; return true; }
+  if (p->generic) { o = mixed_ops(); return true; }
   return get_ops_pow2(p->n, o);
 }
 
 bool get_ops_pow2(int n, Ops& o) {
   switch (n) {
-    case 64: o = ops_for<64>(); return true;
-    case 128: o = ops_for<128>(); return true;
-    case 256: o = ops_for<256>(); return true;
-    case 512: o = ops_for<512>(); return true;
-    case 1024: o = ops_for<1024>(); return true;
-    case 2048: o = ops_for<2048>(); return true;
+    case 64: o = pow2_ops<64>(); return true;
+    case 128: o = pow2_ops<128>(); return true;
+    case 256: o = pow2_ops<256>(); return true;
+    case 512: o = pow2_ops<512>(); return true;
+    case 1024: o = pow2_ops<1024>(); return true;
+    case 2048: o = pow2_ops<2048>(); return true;
   }
   return false;
 }
@@ -598,29 +347,10 @@ void run_col(const Ctx& c, int kind, const ColParams& cp, int nblocks, int label
   c.ops.col(c.p, kind, cp, nblocks, labels, c.s);
 }
 
-template <int N>
-void launch_col_solve(const ColParams& cp, const float* eig, int nblocks, int labels, hipStream_t s) {
-  hipLaunchKernelGGL(k_col_solve<N>, dim3(nblocks, labels), dim3(ColCfg<N>::THREADS), 0, s, cp, eig);
-}
-
 // u-step of the TV model on per-label spectra: Z = V / (1 + eigenvalues) column-wise.
 void run_col_solve(const Ctx& c, const ColParams& cp, int labels) {
-  const shs_plan* p = c.p;
   Timed tm(c.s, KC_COL_SOLVE);
-  if (p->generic) {
-    const size_t e = size_t(p->n) * kGW * sizeof(float2);
-    hipLaunchKernelGGL(k_colg_solve, dim3(p->NS, labels), dim3(256), 2 * e, c.s, cp,
-                       GenParams{p->prow, p->pcol, p->n}, p->eig);
-    return;
-  }
-  switch (p->n) {
-    case 64: launch_col_solve<64>(cp, p->eig, p->NS, labels, c.s); break;
-    case 128: launch_col_solve<128>(cp, p->eig, p->NS, labels, c.s); break;
-    case 256: launch_col_solve<256>(cp, p->eig, p->NS, labels, c.s); break;
-    case 512: launch_col_solve<512>(cp, p->eig, p->NS, labels, c.s); break;
-    case 1024: launch_col_solve<1024>(cp, p->eig, p->NS, labels, c.s); break;
-    case 2048: launch_col_solve<2048>(cp, p->eig, p->NS, labels, c.s); break;
-  }
+  c.ops.col_solve(c.p, cp, labels, c.s);
 }
 
 // S: real images [count][N][N] -> pruned coefficient spectra T1 (count * eta planes).
@@ -1726,33 +1456,12 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
     free_plan(p);
     return fail(SHS_E_DEVICE, "filter generation failed");
   }
-  if (p->generic) {
-    // generic column passes hold their twiddle table and 3 strips of N x 4 bins in dynamic
-    // LDS (up to 104 KB); the cap is set for the largest supported N, so plans of any size
-    // can be created in any order
-    const int lds3 = (3 * kGenericMaxN * kGW + col_tab_len(kGenericMaxN)) * int(sizeof(float2));
-    const int lds2 = (2 * kGenericMaxN * kGW + col_tab_len(kGenericMaxN)) * int(sizeof(float2));
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_colg_syn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds3) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_colg_ana), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds3) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_colg_fwd), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds2) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_colg_final), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds2) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_colg_solve), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds2) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&kg_colg_syn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds3) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&kg_colg_ana), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds3) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&kg_colg_fwd), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds2) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&kg_colg_final), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds2) != hipSuccess) {
-      free_plan(p);
-      return fail(SHS_E_DEVICE, "cannot reserve LDS for the mixed-radix column passes");
-    }
+  // generic column passes hold their twiddle table and 3 strips of N x 4 bins in dynamic LDS
+  // (up to 104 KB); the cap is set for the largest supported N, so plans of any size can be
+  // created in any order
+  if (p->generic && !mixed_reserve_lds()) {
+    free_plan(p);
+    return fail(SHS_E_DEVICE, "cannot reserve LDS for the mixed-radix column passes");
   }
   StripLists sl;
   shs_status st = build_pruned_layout(p, &sl);

@@ -8,7 +8,7 @@
 // v - b_v = g - 2 P(g).  The u-step runs on the DFT: grad^T grad has the eigenvalues
 // e(k0) + e(k1), e(k) = 4 sin^2(pi k / N).
 #pragma once
-#include "generic.hpp"
+#include "kernels.hpp"
 
 namespace shs {
 
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void k_tv_update(TvParams p) {
 }
 
 // Exact energy partials of w: <w, s> and lambda sum_pixels (sum_l |grad w_l|^2)^(1/2).
-__global__ __launch_bounds__(256) void k_tv_energy(TvParams p) {
+static __global__ __launch_bounds__(256) void k_tv_energy(TvParams p) {
   __shared__ double red[4 * 4];
   const long long n2 = (long long)p.n * p.n;
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -184,52 +184,6 @@ __global__ __launch_bounds__(256) void k_tv_energy(TvParams p) {
     double* o = p.partials + (long long)blockIdx.x * 4;
     o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
   }
-}
-
-// u-step on the spectrum: Z = colIFFT( colFFT(V) / (N^2 (1 + e(k0) + e(k1))) ) for every
-// column of q per-label half spectra (eig[k] = e(k), computed on the host in FP64).
-template <int N>
-__global__ __launch_bounds__(ColCfg<N>::THREADS) __attribute__((amdgpu_waves_per_eu(3))) void k_col_solve(
-    ColParams p, const float* __restrict__ eig) {
-  using G = ColCfg<N>;
-  constexpr int R = G::R, T = G::T, W = G::W, M = N / 2;
-  __shared__ float2 lds[col_lds_points<N, R>() * W];
-  const int c = threadIdx.x % W, t = threadIdx.x / W;
-  const int k1 = blockIdx.x * W + c;
-  const bool valid = k1 <= M;
-  const int l = blockIdx.y;
-  const ColAddr<W, R> A{lds + c};
-  const long long strip = l * (long long)N * p.P + (long long)blockIdx.x * (N * W) + c;
-  cpx a[R];
-  static_for<R>([&](auto r) { a[r] = valid ? ld(p.in + strip + (t + r * T) * W) : cpx{0.f, 0.f}; });
-  fft_run<N, R, G::RM, false, SYNC_BLOCK>(a, A, t, p.tw + col_sw_off<N>());
-  const float e1 = valid ? eig[k1] : 0.f;
-  static_for<R>([&](auto r) { a[r] = a[r] * (p.inv_n2 / (1.f + eig[t + r * T] + e1)); });
-  fft_run<N, R, G::RM, true, SYNC_BLOCK>(a, A, t, p.tw + col_sw_off<N>());
-  if (valid) {
-    static_for<R>([&](auto r) { st(p.out + strip + (t + r * T) * W, a[r]); });
-  }
-}
-
-__global__ __launch_bounds__(256) void k_colg_solve(ColParams p, GenParams gp, const float* __restrict__ eig) {
-  extern __shared__ float2 gsm[];
-  const int n = gp.n, E = n * kGW, M = n / 2;
-  float2* b0 = gsm;
-  float2* b1 = gsm + E;
-  const long long strip = blockIdx.y * (long long)n * p.P + (long long)blockIdx.x * E;
-  for (int e = threadIdx.x; e < E; e += 256) b0[e] = p.in[strip + e];
-  __syncthreads();
-  float2* r = gfft<false, SYNC_BLOCK, kGW>(b0, b1, gp.pcol, 256, threadIdx.x, col_sw_g(p.tw, gp.n));
-  float2* o = r == b0 ? b1 : b0;
-  for (int e = threadIdx.x; e < E; e += 256) {
-    const int k1 = blockIdx.x * kGW + (e % kGW);
-    const float m = k1 <= M ? p.inv_n2 / (1.f + eig[e / kGW] + eig[k1]) : 0.f;
-    r[e] = make_float2(r[e].x * m, r[e].y * m);
-  }
-  __syncthreads();
-  float2* z = gfft<true, SYNC_BLOCK, kGW>(r, o, gp.pcol, 256, threadIdx.x, col_sw_g(p.tw, gp.n));
-  for (int e = threadIdx.x; e < E; e += 256)
-    if (blockIdx.x * kGW + (e % kGW) <= M) p.out[strip + e] = z[e];
 }
 
 }  // namespace shs
