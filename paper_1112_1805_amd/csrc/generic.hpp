@@ -13,6 +13,7 @@
 namespace shs {
 
 constexpr int kMaxStages = 10;
+constexpr int kFirstRadix = 32;   // extra radix of a column transform's first stage
 struct FftPlan {
   int L;                     // transform length
   int ns;                    // number of stages
@@ -22,6 +23,8 @@ struct FftPlan {
   unsigned mag[kMaxStages];
   int sh[kMaxStages];
 };
+// LDS buffers of one strip a column transform needs between its stages.
+inline int col_bufs(const FftPlan& pl) { return pl.ns > 2 ? 2 : 1; }
 
 // ---------------------------------------------------------------- small DFTs
 template <int P, bool INV>
@@ -53,276 +56,412 @@ __device__ __forceinline__ void dft_odd_prime(cpx (&a)[P]) {
   });
 }
 
+// Composite radices: they halve the trips through LDS of most sides (32 m needs two stages
+// instead of three).  A * B with coprime factors by the Good-Thomas prime-factor map: input
+// n = (B n1 + A n2) mod R, output k = (B (B^-1 mod A) k1 + A (A^-1 mod B) k2) mod R turn the
+// DFT into an A x B two-dimensional one without twiddles (all index maps are compile-time).
+constexpr int inv_mod(int a, int m) {
+  for (int x = 1; x < m; ++x)
+    if (a * x % m == 1) return x;
+  return 1;
+}
+template <int R, bool INV>
+__device__ __forceinline__ void dft_any(cpx (&a)[R]);
+template <int A, int B, bool INV>
+__device__ __forceinline__ void dft_pfa(cpx (&a)[A * B]) {
+  constexpr int R = A * B, EA = B * inv_mod(B % A, A), EB = A * inv_mod(A % B, B);
+  cpx y[A][B];
+  static_for<A>([&](auto i) {
+    static_for<B>([&](auto j) { y[i][j] = a[(B * i + A * j) % R]; });
+    dft_any<B, INV>(y[i]);
+  });
+  static_for<B>([&](auto j) {
+    cpx z[A];
+    static_for<A>([&](auto i) { z[i] = y[i][j]; });
+    dft_any<A, INV>(z);
+    static_for<A>([&](auto i) { a[(EA * i + EB * j) % R] = z[i]; });
+  });
+}
+
 template <int R, bool INV>
 __device__ __forceinline__ void dft_any(cpx (&a)[R]) {
-  if constexpr (R == 2 || R == 4 || R == 8 || R == 16) {
-    RegDFT<R, INV>::run(a);
-  } else if constexpr (R == 9) {
-    reg_dft_split<9, 3, 3, INV>(a);
-  } else {
-    dft_odd_prime<R, INV>(a);
+  if constexpr (R == 2 || R == 3 || R == 4 || R == 8 || R == 16 || R == 32) RegDFT<R, INV>::run(a);
+  else if constexpr (R == 9) reg_dft_split<9, 3, 3, INV>(a);
+  else if constexpr (R == 6) dft_pfa<2, 3, INV>(a);
+  else if constexpr (R == 10) dft_pfa<2, 5, INV>(a);
+  else if constexpr (R == 12) dft_pfa<4, 3, INV>(a);
+  else if constexpr (R == 14) dft_pfa<2, 7, INV>(a);
+  else if constexpr (R == 15) dft_pfa<3, 5, INV>(a);
+  else if constexpr (R == 18) dft_pfa<2, 9, INV>(a);
+  else if constexpr (R == 20) dft_pfa<4, 5, INV>(a);
+  else if constexpr (R == 22) dft_pfa<2, 11, INV>(a);
+  else if constexpr (R == 24) dft_pfa<8, 3, INV>(a);
+  else dft_odd_prime<R, INV>(a);
+}
+
+// The radices a stage can have; with_radix calls f with the radix as a compile-time value.
+#define SHS_RADICES(X)                                                                     \
+  X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17)  \
+  X(18) X(19) X(20) X(22) X(23) X(24)
+template <class F>
+__device__ __forceinline__ void with_radix(int r, F&& f) {
+  switch (r) {
+#define SHS_CASE(RR) \
+    case RR: f(std::integral_constant<int, RR>{}); break;
+    SHS_RADICES(SHS_CASE)
+#undef SHS_CASE
+    default: break;
   }
 }
 
 // ---------------------------------------------------------------- one Stockham stage
-// `items` = W interleaved transforms x (L / R) butterflies, spread over nthr threads.
-// Element `pos` of transform c lives at buf[pos * W + c].
-// sw: stage twiddles of the whole transform in thread read order, W_{Ns R}^{i k} at
+// `items` = 2^lw interleaved transforms x (L / R) butterflies, spread over nthr threads;
+// item it is butterfly it >> lw of transform it mod 2^lw.
+// `early(bf, c)` issues loads whose values only `done` needs; `load(a, bf, nb, c)` fills the
+// inputs, a[i] = element bf + i nb (nb = L/R) of transform c; `done(a, ob, bf, c, e)` takes
+// the R outputs, output i belonging to position ob + i Ns, and what `early` returned.  So a
+// transform's first stage can read global memory and its last one can write there (or go on
+// with the data in registers): in the last stage ob = bf and Ns = nb, so a butterfly's outputs
+// are the positions of its inputs.  Loads are issued for the whole butterfly before any is
+// used: a wave runs alone with its latencies where the GPU is not full.
+// sw: stage twiddles of the whole transform in thread read order (LDS), W_{Ns R}^{i k} at
 // sw[i Ns + k - 1] (1 <= i < R, k < Ns) for the stage of stride Ns and radix R; the stages'
 // ranges [Ns - 1, Ns R - 1) tile [0, L - 1), and consecutive butterflies read consecutive
 // entries.
-// TWL: sw is a copy of the table in LDS and every twiddle power is read from it (no
-// products, no vector-memory loads); otherwise the power-of-two exponents are loaded from
-// global memory and the others formed by products.
-template <int R, bool INV, int W, bool TWL>
-__device__ __forceinline__ void gstage(const float2* __restrict__ src, float2* __restrict__ dst, int L, int Ns,
-                                       unsigned mag, int sh, int nthr, int tid, const float2* __restrict__ sw) {
-  static_assert((W & (W - 1)) == 0, "strip width is a power of two");
-  const int nb = L / R;
-  const int items = nb * W;
+struct StageGeom {
+  int L, Ns;
+  unsigned mag;
+  int sh;
+};
+__device__ __forceinline__ StageGeom stage_geom(const FftPlan& pl, int s, int Ns) {
+  return StageGeom{pl.L, Ns, pl.mag[s], pl.sh[s]};
+}
+// What `early` loaded, or (EARLY = false) what `now` loads.
+template <bool EARLY, class E, class F>
+__device__ __forceinline__ auto early_or(const E& e, F&& now) {
+  if constexpr (EARLY) return e;
+  else return now();
+}
+struct NoEarly {
+  __device__ __forceinline__ int operator()(int, int) const { return 0; }
+};
+template <int R, bool INV, class Early, class Load, class Done>
+__device__ __forceinline__ void gstage(const StageGeom& q, int lw, int nthr, int tid, const float2* sw, Early&& early,
+                                       Load&& load, Done&& done) {
+  const int nb = q.L / R;
+  const int items = nb << lw;
   for (int it = tid; it < items; it += nthr) {
-    const int c = it & (W - 1);
-    const unsigned bf = unsigned(it) / W;
-    const unsigned g = (__umulhi(bf, mag) + bf) >> sh;     // bf / Ns
-    const int k = int(bf - g * unsigned(Ns));
+    const int c = it & ((1 << lw) - 1);
+    const unsigned bf = unsigned(it) >> lw;
+    unsigned g = bf;
+    int k = 0;
+    if (q.Ns > 1) {
+      g = (__umulhi(bf, q.mag) + bf) >> q.sh;     // bf / Ns
+      k = int(bf - g * unsigned(q.Ns));
+    }
+    const auto e = early(int(bf), c);
     cpx a[R];
-    static_for<R>([&](auto i) { a[i] = ld(src + (int(bf) + i * nb) * W + c); });
-    if (Ns > 1) {
-      // z^i with z = W_{Ns R}^k: the power-of-two exponents are loaded, the others are
-      // products of two of them (fewer loads through the vector-memory data path)
-      cpx w[R];
-      if constexpr (TWL) {
-        static_for<R>([&](auto i) {
-          if constexpr (i > 0) w[i] = ld(sw + (i * Ns + k - 1));
-        });
-      } else {
-        static_for<R>([&](auto i) {
-          if constexpr (i > 0 && (i & (i - 1)) == 0) w[i] = ld(sw + (i * Ns + k - 1));
-        });
-        static_for<R>([&](auto i) {
-          if constexpr (i > 0 && (i & (i - 1)) != 0) {
-            constexpr int hi = 1 << (31 - __builtin_clz(unsigned(i)));
-            w[i] = cmul(w[hi], w[i - hi]);
-          }
-        });
-      }
+    load(a, int(bf), nb, c);
+    if (q.Ns > 1) {
       static_for<R - 1>([&](auto i1) {
         constexpr int i = i1 + 1;
-        a[i] = INV ? cmulc(a[i], w[i]) : cmul(a[i], w[i]);
+        const cpx w = ld(sw + (i * q.Ns + k - 1));
+        a[i] = INV ? cmulc(a[i], w) : cmul(a[i], w);
       });
     }
     dft_any<R, INV>(a);
-    const int ob = int(g) * Ns * R + k;
-    static_for<R>([&](auto i) { st(dst + (ob + i * Ns) * W + c, a[i]); });
+    done(a, int(g) * q.Ns * R + k, int(bf), c, e);
   }
 }
 
-// Full transform: data in b0 (natural order) -> result (natural order) in the returned buffer.
-template <bool INV, int SK, int W, bool TWL = false>
-__device__ __forceinline__ float2* gfft(float2* b0, float2* b1, const FftPlan& pl, int nthr, int tid, const float2* __restrict__ sw) {
-  float2* src = b0;
-  float2* dst = b1;
-  int Ns = 1;
-  for (int s = 0; s < pl.ns; ++s) {
+// Element accesses of LDS-resident data: position pos of transform c at buf[pos 2^lw + c].
+struct LdsRead {
+  const float2* buf;
+  int lw;
+  template <int R>
+  __device__ __forceinline__ void operator()(cpx (&a)[R], int bf, int nb, int c) const {
+    static_for<R>([&](auto i) { a[i] = ld(buf + (((bf + i * nb) << lw) + c)); });
+  }
+};
+struct LdsWrite {
+  float2* buf;
+  int lw, Ns;
+  template <int R>
+  __device__ __forceinline__ void operator()(cpx (&a)[R], int ob, int, int c, int = 0) const {
+    static_for<R>([&](auto i) { st(buf + (((ob + i * Ns) << lw) + c), a[i]); });
+  }
+};
+
+// The stages [s0, s1) of a transform between LDS buffers, starting in `cur`; returns the
+// buffer that holds the result (alt == cur is allowed where every stage is one pass of one
+// wave, whose reads all precede its writes).  Ns: stride of stage s0 on entry, of s1 on exit.
+template <bool INV, int SK>
+__device__ __forceinline__ float2* gfft_stages(const FftPlan& pl, int s0, int s1, int& Ns, float2* cur, float2* alt,
+                                               int lw, int nthr, int tid, const float2* sw) {
+  for (int s = s0; s < s1; ++s) {
     const int r = pl.radix[s];
-    const unsigned mg = pl.mag[s];
-    const int sh = pl.sh[s];
-    switch (r) {
-      case 2: gstage<2, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 3: gstage<3, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 4: gstage<4, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 5: gstage<5, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 7: gstage<7, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 8: gstage<8, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 9: gstage<9, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 11: gstage<11, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 13: gstage<13, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 16: gstage<16, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 17: gstage<17, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 19: gstage<19, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      case 23: gstage<23, INV, W, TWL>(src, dst, pl.L, Ns, mg, sh, nthr, tid, sw); break;
-      default: break;
-    }
+    const StageGeom q = stage_geom(pl, s, Ns);
+    with_radix(r, [&](auto R) __attribute__((always_inline)) {
+      gstage<R, INV>(q, lw, nthr, tid, sw, NoEarly{}, LdsRead{cur, lw}, LdsWrite{alt, lw, q.Ns});
+    });
     fft_sync<SK>();
-    float2* t = src;
-    src = dst;
-    dst = t;
+    float2* t = cur;
+    cur = alt;
+    alt = t;
     Ns *= r;
   }
-  return src;
+  return cur;
 }
 
 // ---------------------------------------------------------------- generic geometry
 constexpr int kGW = 4;          // strip width of the generic path
-
+constexpr int kGLW = 2;         // its logarithm
 
 struct GenParams {
-  FftPlan prow;   // length N/2
-  FftPlan pcol;   // length N
+  FftPlan pinv;   // inverse row transform, length N/2
+  FftPlan pfwd;   // forward row transform: the same stages in reverse order
+  FftPlan pcol;   // column transforms, length N
   int n;
   int wpb;        // waves per row-pass block (1, 2 or 4; the block is 64 wpb threads)
+  int lrw;        // log2 of the rows per wave
+  int nbuf;       // LDS buffers per row-pass wave: 1 where every stage is one pass, else 2
 };
-// Twiddle table of a mixed-radix plan, one device array: [0, N) exp(-2 pi i m / N), then
-// the stage table of the row FFT (N/2 entries), then that of the column FFT (N entries).
+// Twiddle table of a mixed-radix plan, one device array: [0, N) exp(-2 pi i m / N); then what
+// a row pass copies, 3 N/2 entries (see row_tab_len); then the column transform's stage table
+// (N entries).
 __device__ __forceinline__ const float2* row_sw_g(const float2* tw, int n) { return tw + n; }
-__device__ __forceinline__ const float2* col_sw_g(const float2* tw, int n) { return tw + n + n / 2; }
+__device__ __forceinline__ const float2* col_sw_g(const float2* tw, int n) { return tw + n + 3 * (n / 2); }
 
 // The kernels below keep their twiddles in LDS, at the start of the dynamic shared memory
 // (loaded once per block): the mixed-radix stages read one table entry per twiddle, where
 // loads from global memory would compete with the data for the vector-memory path.
-//   row pass:     exp(-2 pi i k / N) for k <= N/2, then the row FFT's stage table
+//   row pass:     exp(-2 pi i k / N) for k <= N/2, then the two stage tables (N/2 - 1 each)
 //   column pass:  the column FFT's stage table (N - 1 entries, padded to N)
-__host__ __device__ constexpr int row_tab_len(int n) { return n; }       // (N/2 + 1) + (N/2 - 1)
+__host__ __device__ constexpr int row_tab_len(int n) { return 3 * (n / 2); }
 __host__ __device__ constexpr int col_tab_len(int n) { return n; }
 __device__ __forceinline__ void load_table(float2* dst, const float2* __restrict__ src, int len) {
-  for (int e = threadIdx.x; e < len; e += blockDim.x) dst[e] = src[e];
+#pragma unroll 4
+  for (int e = threadIdx.x; e < len; e += blockDim.x) dst[e] = src[e];   // loads of four entries in flight
 }
 
 // ---------------------------------------------------------------- generic row pass
-// Same modes and data contract as k_row.  Each wave transforms RW rows at once, stored
-// interleaved in LDS (bin k of row c at k * RW + c, two half-length complex buffers per
-// wave, dynamic shared memory), so that a stage's butterflies of all RW rows share the
-// wave's lanes; memory phases walk one row at a time (coalesced along the row).  A block
-// holds gp.wpb waves: more rows per wave fill the lanes in stages with few butterflies
-// (a large radix), fewer waves per block keep such blocks within their LDS share.
+// Same modes and data contract as k_row.  Each wave transforms 2^lrw rows at once, stored
+// interleaved in LDS (bin k of row c at k 2^lrw + c), so that a stage's butterflies of all
+// its rows share the wave's lanes.  A block holds gp.wpb waves: more rows per wave fill the
+// lanes in stages with few butterflies (a large radix), fewer waves per block keep such
+// blocks within their LDS share.
+//
+// The pass is bound by VALU issue and LDS traffic together, so the data stay in registers
+// wherever one butterfly's outputs are another's inputs: the inverse transform's first stage
+// reads the spectrum from global memory (with the real-FFT pre-processing), and its last
+// stage, the state update and the forward transform's first stage are one butterfly, because
+// the forward transform runs the same radices in reverse order (outputs and inputs of both
+// are the positions bf + i M/R).  Measured with the column passes' like change, against every
+// stage as a pass over LDS with power-of-two and prime radices: 32 images of 96..768, FP32
+// state, 10.7 -> 8.0 ms per iteration; 360^2, q = 2, FP16, 143 -> 105 us; adjoint of five
+// 736^2 images 632 -> 425 us.
 __device__ __forceinline__ int tix_g(int ip, int row, int n) {
   return (ip >> 2) * (n * kGW) + row * kGW + (ip & (kGW - 1));     // floor for negative ip
 }
 
-template <int MODE, int ST, bool STATS, int RW>
+template <class Pair, int R> struct StatePairs { Pair v[R]; };
+
+template <int MODE, int ST, bool STATS>
 __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& gp, BlockId bid) {
   static_assert(kGW == 4, "tix_g assumes strips of 4 columns");
   using S = Store<ST>;
   extern __shared__ float2 gsm[];
   __shared__ double red[4 * 4];
-  const int n = gp.n, M = n / 2;
+  constexpr bool HALVED = MODE == ROW_SOLVE || MODE == ROW_PRIME;   // next adjoint input passed on halved
+  const int n = gp.n, M = n / 2, lw = gp.lrw;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row0 = (bid.x * gp.wpb + wave) * RW;
+  const int row0 = (bid.x * gp.wpb + wave) << lw;
   const int ch = bid.y;
   const int j = ch % p.eta;
-  float2* ltw = gsm;                 // exp(-2 pi i k / N), k <= M
-  float2* lsw = gsm + M + 1;         // row FFT stage table
-  load_table(ltw, p.tw, M + 1);
-  load_table(lsw, row_sw_g(p.tw, n), M - 1);
-  float2* b0 = gsm + row_tab_len(n) + wave * 2 * M * RW;
-  float2* b1 = b0 + M * RW;
+  const int last = gp.pinv.ns - 1;
+  float2* ltw = gsm;                     // exp(-2 pi i k / N), k <= M
+  float2* isw = gsm + M + 1;             // inverse row transform's stage table
+  float2* fsw = isw + M - 1;             // forward row transform's
+  load_table(ltw, row_sw_g(p.tw, n), 3 * M - 1);
+  float2* cur = gsm + row_tab_len(n) + ((wave * gp.nbuf * M) << lw);
+  float2* alt = cur + (gp.nbuf == 2 ? (M << lw) : 0);
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  float2* res = b0;
+  bool emit = true;
+  if constexpr (MODE == ROW_SOLVE) emit = p.emit != 0;
   __syncthreads();
 
+  const float th = p.fw.thr[j];
+  const auto state = [&](int c) {
+    return reinterpret_cast<typename S::T*>(p.g) + (long long)ch * n * n + (long long)(row0 + c) * n;
+  };
   if constexpr (MODE == ROW_SOLVE || MODE == ROW_C2R || MODE == ROW_ENERGY || MODE == ROW_SHRINK || MODE == ROW_PD) {
     int cb, pitch;
     long long off;
     plane_geom(p.lin, ch % p.lin.nf, cb, pitch, off);
     const PlaneBuf B(p.spec_in + (ch / p.lin.nf) * p.lin.ls + off, pitch * n);
-    for (int c = 0; c < RW; ++c) {
-      const int row = row0 + c;
-      for (int k = lane; k < M; k += 64) {
-        // bins outside the plane's columns are out-of-range buffer loads: zero
-        const cpx xp = B.load(tix_g(k - cb, row, n));
-        const cpx xm = conj(B.load(tix_g(M - k - cb, row, n)));
-        const cpx s = xp + xm, d = xp - xm;
-        const cpx w = conj(ld(ltw + k));
-        st(b0 + k * RW + c, s + mul_i(cmul(d, w)));
-      }
-    }
+    // first stage: z[k] = s + i d W_N^{-k} with s = X[k] + conj(X[M-k]), d = X[k] - conj(X[M-k]);
+    // bins outside the plane's columns are out-of-range buffer loads (zero), and whole chunks
+    // [i nb, i nb + nb) that miss the window directly or mirrored are skipped
+    with_radix(gp.pinv.radix[0], [&](auto R) __attribute__((always_inline)) {
+      gstage<R, true>(stage_geom(gp.pinv, 0, 1), lw, 64, lane, isw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
+        const auto in_p = [&](int k0) { return k0 < cb + pitch && k0 + nb > cb; };
+        const auto in_m = [&](int k0) { return k0 <= M - cb && k0 + nb > M - cb - pitch; };
+        // in groups of 8 bins: their mirrored bins' registers bound the butterfly's footprint
+        constexpr int H = 8;
+        static_for<(R + H - 1) / H>([&](auto h) {
+          constexpr int i0 = h * H, cnt = R - i0 < H ? R - i0 : H;
+          cpx xm[H];
+          static_for<cnt>([&](auto m) {
+            constexpr int i = i0 + m;
+            const int k = bf + i * nb;
+            a[i] = cpx{0.f, 0.f};
+            xm[m] = cpx{0.f, 0.f};
+            if (in_p(i * nb)) a[i] = B.load(tix_g(k - cb, row0 + c, n));
+            if (in_m(i * nb)) xm[m] = B.load(tix_g(M - k - cb, row0 + c, n));
+          });
+          static_for<cnt>([&](auto m) {
+            constexpr int i = i0 + m;
+            if (in_p(i * nb) || in_m(i * nb)) {
+              const cpx s = a[i] + conj(xm[m]), d = a[i] - conj(xm[m]);
+              const cpx w = ld(ltw + (bf + i * nb));   // W_N^k
+              a[i] = cpx{fmaf(d.x, w.y, fmaf(-d.y, w.x, s.x)), fmaf(d.x, w.x, fmaf(d.y, w.y, s.y))};
+            }
+          });
+        });
+      }, LdsWrite{cur, lw, 1});
+    });
     fft_sync<SYNC_WAVE>();
-    res = gfft<true, SYNC_WAVE, RW, true>(b0, b1, gp.prow, 64, lane, lsw);
-  }
-  if constexpr (MODE == ROW_C2R) {
-    for (int c = 0; c < RW; ++c) {
-      float* out = p.real_out + ch * p.real_cs + (long long)(row0 + c) * n;
-      for (int k = lane; k < M; k += 64) *reinterpret_cast<float2*>(out + 2 * k) = res[k * RW + c];
-    }
-    return;
-  }
-  if constexpr (MODE == ROW_ENERGY) {
-    for (int e = lane; e < M * RW; e += 64) acc[SLOT_L1] += fabsf(res[e].x) + fabsf(res[e].y);
-  }
-  if constexpr (MODE == ROW_R2C) {
-    for (int c = 0; c < RW; ++c) {
-      const float* in = p.real_in + ch * p.real_cs + (long long)(row0 + c) * n;
-      for (int k = lane; k < M; k += 64) res[k * RW + c] = *reinterpret_cast<const float2*>(in + 2 * k);
-    }
-  }
-  if constexpr (MODE == ROW_SOLVE || MODE == ROW_PRIME) {
-    const float th = p.fw.thr[j];
-    for (int c = 0; c < RW; ++c) {
-      typename S::T* g = reinterpret_cast<typename S::T*>(p.g) + (long long)ch * n * n + (long long)(row0 + c) * n;
-      for (int k = lane; k < M; k += 64) {
-        float g0, g1;
-        S::unpack(S::load_pair(g + 2 * k), g0, g1);
-        const float b0v = clip(g0, th), b1v = clip(g1, th);
-        float n0 = g0, n1 = g1;
+    int Ns = gp.pinv.radix[0];
+    float2* res = gfft_stages<true, SYNC_WAVE>(gp.pinv, 1, last, Ns, cur, alt, lw, 64, lane, isw);
+    alt = res == cur ? alt : cur;
+    cur = res;
+    // last stage, update, and the forward transform's first stage
+    with_radix(gp.pinv.radix[last], [&](auto R) __attribute__((always_inline)) {
+      const int nb = M / R;
+      // the state's pairs: loaded before the butterfly where its registers allow, else after it
+      constexpr bool STATE = MODE == ROW_SOLVE || MODE == ROW_PD;
+      constexpr bool EARLY = STATE && R * sizeof(typename S::Pair) <= 64;
+      const auto load_state = [&](int bf, int c) {
+        StatePairs<typename S::Pair, STATE ? int(R) : 1> e;
+        const typename S::T* g = state(c);
+        static_for<R>([&](auto i) { e.v[i] = S::load_pair(g + 2 * (bf + i * nb)); });
+        return e;
+      };
+      const auto early = [&](int bf, int c) {
+        if constexpr (EARLY) return load_state(bf, c);
+        else return 0;
+      };
+      gstage<R, true>(stage_geom(gp.pinv, last, Ns), lw, 64, lane, isw, early, LdsRead{cur, lw},
+                      [&](cpx (&a)[R], int, int bf, int c, const auto& e0) {
+        if constexpr (MODE == ROW_C2R) {
+          float* out = p.real_out + ch * p.real_cs + (long long)(row0 + c) * n;
+          static_for<R>([&](auto i) {
+            *reinterpret_cast<float2*>(out + 2 * (bf + i * nb)) = make_float2(a[i].x, a[i].y);
+          });
+        }
+        if constexpr (MODE == ROW_ENERGY) {
+          static_for<R>([&](auto i) { acc[SLOT_L1] += fabsf(a[i].x) + fabsf(a[i].y); });
+        }
         if constexpr (MODE == ROW_SOLVE) {
-          const float2 cc = res[k * RW + c];
-          n0 = b0v + cc.x;
-          n1 = b1v + cc.y;
-          S::store_pair(g + 2 * k, S::round2(n0, n1));
+          typename S::T* g = state(c);
+          const auto e = early_or<EARLY>(e0, [&] { return load_state(bf, c); });
+          static_for<R>([&](auto i) {
+            const int k = bf + i * nb;
+            float g0, g1;
+            S::unpack(e.v[i], g0, g1);
+            const float b0v = clip(g0, th), b1v = clip(g1, th);
+            // g <- clip(g) + S_j u  (v = shrink(g), b_v = clip(g); Section 3 v- and b_v-updates)
+            float n0 = b0v + a[i].x, n1 = b1v + a[i].y;
+            S::store_pair(g + 2 * k, S::round2(n0, n1));
+            const float nb0 = clip(n0, th), nb1 = clip(n1, th);
+            if constexpr (STATS) {
+              const float dv0 = (n0 - nb0) - (g0 - b0v), dv1 = (n1 - nb1) - (g1 - b1v);
+              const float db0 = nb0 - b0v, db1 = nb1 - b1v;
+              acc[SLOT_DY2] = fmaf(dv0, dv0, acc[SLOT_DY2]);
+              acc[SLOT_DY2] = fmaf(dv1, dv1, acc[SLOT_DY2]);
+              acc[SLOT_DB2] = fmaf(db0, db0, acc[SLOT_DB2]);
+              acc[SLOT_DB2] = fmaf(db1, db1, acc[SLOT_DB2]);
+              acc[SLOT_L1] += fabsf(n0 - nb0);
+              acc[SLOT_L1] += fabsf(n1 - nb1);
+            }
+            a[i] = cpx{fmaf(0.5f, n0, -nb0), fmaf(0.5f, n1, -nb1)};
+          });
+          // complete the residual sums here: sunk past the next butterfly they would keep
+          // every per-pixel term live
+          if constexpr (STATS) __asm__ volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[3]));
         }
-        const float nb0 = clip(n0, th), nb1 = clip(n1, th);
-        if constexpr (STATS && MODE == ROW_SOLVE) {
-          const float dv0 = (n0 - nb0) - (g0 - b0v), dv1 = (n1 - nb1) - (g1 - b1v);
-          const float db0 = nb0 - b0v, db1 = nb1 - b1v;
-          acc[SLOT_DY2] = fmaf(dv0, dv0, acc[SLOT_DY2]);
-          acc[SLOT_DY2] = fmaf(dv1, dv1, acc[SLOT_DY2]);
-          acc[SLOT_DB2] = fmaf(db0, db0, acc[SLOT_DB2]);
-          acc[SLOT_DB2] = fmaf(db1, db1, acc[SLOT_DB2]);
-          acc[SLOT_L1] += fabsf(n0 - nb0);
-          acc[SLOT_L1] += fabsf(n1 - nb1);
+        if constexpr (MODE == ROW_PD) {
+          // dual step of the primal-dual iteration: y <- clip(y + sigma c, +-lambda_j), c = (K ubar)_j
+          typename S::T* g = state(c);
+          const auto e = early_or<EARLY>(e0, [&] { return load_state(bf, c); });
+          static_for<R>([&](auto i) {
+            const int k = bf + i * nb;
+            float y0, y1;
+            S::unpack(e.v[i], y0, y1);
+            float n0 = clip(fmaf(p.sigma, a[i].x, y0), th);
+            float n1 = clip(fmaf(p.sigma, a[i].y, y1), th);
+            S::store_pair(g + 2 * k, S::round2(n0, n1));
+            if constexpr (STATS) {
+              const float d0 = n0 - y0, d1 = n1 - y1;
+              acc[SLOT_DY2] += d0 * d0 + d1 * d1;
+              acc[SLOT_L1] += fabsf(a[i].x) + fabsf(a[i].y);
+            }
+            a[i] = cpx{n0, n1};
+          });
+          if constexpr (STATS) __asm__ volatile("" : "+v"(acc[0]), "+v"(acc[3]));
         }
-        res[k * RW + c] = make_float2(n0 - 2.f * nb0, n1 - 2.f * nb1);
-      }
-    }
-  }
-  if constexpr (MODE == ROW_PD) {
-    const float th = p.fw.thr[j];
-    for (int c = 0; c < RW; ++c) {
-      typename S::T* g = reinterpret_cast<typename S::T*>(p.g) + (long long)ch * n * n + (long long)(row0 + c) * n;
-      for (int k = lane; k < M; k += 64) {
-        float y0, y1;
-        S::unpack(S::load_pair(g + 2 * k), y0, y1);
-        const float2 cc = res[k * RW + c];
-        float n0 = clip(fmaf(p.sigma, cc.x, y0), th);
-        float n1 = clip(fmaf(p.sigma, cc.y, y1), th);
-        S::store_pair(g + 2 * k, S::round2(n0, n1));
-        if constexpr (STATS) {
-          const float d0 = n0 - y0, d1 = n1 - y1;
-          acc[SLOT_DY2] += d0 * d0 + d1 * d1;
-          acc[SLOT_L1] += fabsf(cc.x) + fabsf(cc.y);
+        if constexpr (MODE == ROW_SHRINK) {
+          static_for<R>([&](auto i) { a[i] = cpx{a[i].x - clip(a[i].x, th), a[i].y - clip(a[i].y, th)}; });
         }
-        res[k * RW + c] = make_float2(n0, n1);
-      }
-    }
+        if constexpr (MODE == ROW_SOLVE || MODE == ROW_PD || MODE == ROW_SHRINK) {
+          if (emit) {
+            dft_any<R, false>(a);
+            LdsWrite{alt, lw, 1}(a, bf * R, bf, c);
+          }
+        }
+      });
+    });
   }
-  if constexpr (MODE == ROW_SHRINK) {
-    const float th = p.fw.thr[j];
-    for (int e = lane; e < M * RW; e += 64) {
-      const float2 c = res[e];
-      res[e] = make_float2(c.x - clip(c.x, th), c.y - clip(c.y, th));
-    }
+  if constexpr (MODE == ROW_C2R) return;
+  if constexpr (MODE == ROW_R2C || MODE == ROW_PRIME) {
+    with_radix(gp.pfwd.radix[0], [&](auto R) __attribute__((always_inline)) {
+      gstage<R, false>(stage_geom(gp.pfwd, 0, 1), lw, 64, lane, fsw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
+        if constexpr (MODE == ROW_R2C) {
+          const float* in = p.real_in + ch * p.real_cs + (long long)(row0 + c) * n;
+          static_for<R>([&](auto i) { a[i] = ld(reinterpret_cast<const float2*>(in + 2 * (bf + i * nb))); });
+        } else {
+          const typename S::T* g = state(c);
+          static_for<R>([&](auto i) {
+            float g0, g1;
+            S::unpack(S::load_pair(g + 2 * (bf + i * nb)), g0, g1);
+            a[i] = cpx{fmaf(0.5f, g0, -clip(g0, th)), fmaf(0.5f, g1, -clip(g1, th))};
+          });
+        }
+      }, LdsWrite{alt, lw, 1});
+    });
   }
-  if constexpr (MODE == ROW_R2C || MODE == ROW_PRIME || MODE == ROW_SOLVE || MODE == ROW_SHRINK || MODE == ROW_PD) {
-    bool emit = true;
-    if constexpr (MODE == ROW_SOLVE) emit = p.emit != 0;
+  if constexpr (MODE != ROW_ENERGY) {
     if (emit) {
       fft_sync<SYNC_WAVE>();
-      float2* other = res == b0 ? b1 : b0;
-      float2* Y = gfft<false, SYNC_WAVE, RW, true>(res, other, gp.prow, 64, lane, lsw);
+      int Ns = gp.pfwd.radix[0];
+      const float2* Y = gfft_stages<false, SYNC_WAVE>(gp.pfwd, 1, last + 1, Ns, alt, cur, lw, 64, lane, fsw);
       int cb, pitch;
       long long off;
       plane_geom(p.lout, ch % p.lout.nf, cb, pitch, off);
       const PlaneBuf B(p.spec_out + (ch / p.lout.nf) * p.lout.ls + off, pitch * n);
-      for (int c = 0; c < RW; ++c) {
-        const int row = row0 + c;
-        for (int k = lane; k <= M; k += 64) {
-          // stores of bins outside the plane's columns are dropped (out-of-range buffer stores)
-          const cpx yk = ld(Y + (k == M ? 0 : k) * RW + c);
-          const cpx ym = conj(ld(Y + (k == 0 ? 0 : M - k) * RW + c));
-          const cpx s = yk + ym, d = yk - ym;
-          const cpx w = ld(ltw + k);
-          B.store(tix_g(k - cb, row, n), (s - mul_i(cmul(d, w))) * 0.5f);
-        }
+      // bins k and M - k of a row come from the same two points: X[k] = (s - i d W^k) / 2 and
+      // X[M-k] = conj(s + i d W^k) / 2 with s = Y[k] + conj(Y[M-k]), d = Y[k] - conj(Y[M-k]);
+      // stores outside the plane's columns are dropped (out-of-range buffer stores)
+      const float hs = HALVED ? 1.f : 0.5f;
+      const int items = (M / 2 + 1) << lw;
+      for (int it = lane; it < items; it += 64) {
+        const int c = it & ((1 << lw) - 1), k = it >> lw, row = row0 + c;
+        const cpx yk = ld(Y + it);
+        const cpx ym = conj(ld(Y + (((k == 0 ? 0 : M - k) << lw) + c)));
+        const cpx s = yk + ym, d = yk - ym;
+        const cpx e = mul_i(cmul(d, ld(ltw + k)));
+        B.store(tix_g(k - cb, row, n), (s - e) * hs);
+        B.store(tix_g(M - k - cb, row, n), conj(s + e) * hs);
       }
     }
   }
@@ -337,9 +476,9 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
   }
 }
 
-template <int MODE, int ST, bool STATS, int RW>
-__global__ __launch_bounds__(256) void k_row_g(RowParams p, GenParams gp) {
-  row_g_body<MODE, ST, STATS, RW>(p, gp, own_block());
+template <int MODE, int ST, bool STATS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_row_g(RowParams p, GenParams gp) {
+  row_g_body<MODE, ST, STATS>(p, gp, own_block());
 }
 
 }  // namespace shs

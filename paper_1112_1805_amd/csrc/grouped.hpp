@@ -69,11 +69,11 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS) __attribute__((amdgpu_waves_per
 }
 
 // ---- mixed-radix sizes (runtime N; dynamic LDS sized for the group's largest image)
-template <int MODE, int ST, bool STATS, int RW>
-__global__ __launch_bounds__(256) void kg_row_g(const GroupTask<RowParams>* __restrict__ tasks,
+template <int MODE, int ST, bool STATS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void kg_row_g(const GroupTask<RowParams>* __restrict__ tasks,
                                                 const uint16_t* __restrict__ bt) {
   const GroupTask<RowParams>& T = group_task(tasks, bt);
-  row_g_body<MODE, ST, STATS, RW>(T.p, T.gp, group_block(T));
+  row_g_body<MODE, ST, STATS>(T.p, T.gp, group_block(T));
 }
 
 // ---- pixel step (any size)

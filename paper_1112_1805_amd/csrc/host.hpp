@@ -19,7 +19,8 @@ struct shs_plan {
   int rpb;             // rows per row-pass block
   int rw;              // generic path: rows per wave of the row pass (1, 2 or 4)
   int wpb;             // generic path: waves per row-pass block (1, 2 or 4)
-  FftPlan prow, pcol;  // mixed-radix stage lists (generic path)
+  int nbuf;            // generic path: LDS buffers per row-pass wave (row_g_bufs)
+  FftPlan prow, pfwd, pcol;  // mixed-radix transforms: inverse rows, forward rows, columns
   float* psi;          // [eta][N][PP] dense filter bank (half spectrum)
   float2* tw;          // [N] exp(-2 pi i m / N), then (power-of-two N) the FFT stage tables
   float* eig;          // [N] 4 sin^2(pi k / N): DFT eigenvalues of one forward-difference pair (TV)
@@ -29,9 +30,10 @@ struct shs_plan {
   int4* tcol;          // [eta] {cb, pitch, off_lo, off_hi} of the filtered spectra
   long long t_ls;      // label stride of the filtered spectra (float2)
   // column work lists
-  int4* items_syn;     // {strip, flist offset, count, -1}
-  int4* items_ana;     // {strip, flist offset, count, partial slot or -1}
-  int* flist;          // filter ids, grouped by strip
+  int4* items_syn;     // {strip, first work-list entry, count, -1}
+  int4* items_ana;     // {strip, first work-list entry, count, partial slot or -1}
+  int4* fwin;          // work list, entries grouped by strip: column windows [entry][W]
+  int4* fgeo;          // and plane geometry [entry]
   int2* strips_ana;    // per strip {first analysis item, items}
   int n_syn, n_ana, n_part;
   int fc_syn;          // filters per synthesis work item
@@ -131,10 +133,29 @@ Ops mixed_ops();
 constexpr int kGenericMaxN = 1024;          // largest image side of the mixed-radix path
 constexpr size_t kRowGLdsMax = 64 * 1024;   // dynamic LDS a generic row block may take
 
-// Dynamic LDS of a generic row-pass block: two half-length buffers of rw rows per wave,
-// then the twiddle tables.
-inline size_t row_g_lds_bytes(int M, int rw, int wpb, int n) {
-  return (size_t(wpb) * 2 * M * rw + row_tab_len(n)) * sizeof(float2);
+// LDS buffers a row-pass wave needs for rw rows: one where every stage is a single pass over
+// the wave's 64 lanes (all its reads precede its writes), else two.
+inline int row_g_bufs(const FftPlan& pl, int rw) {
+  int rmin = pl.radix[0];
+  for (int i = 1; i < pl.ns; ++i) rmin = pl.radix[i] < rmin ? pl.radix[i] : rmin;
+  return pl.L / rmin * rw <= 64 ? 1 : 2;
+}
+// Dynamic LDS of a generic row-pass block: the twiddle tables and each wave's buffers.
+inline size_t row_g_lds_bytes(int M, int rw, int wpb, int nbuf) {
+  return (size_t(wpb) * nbuf * M * rw + row_tab_len(2 * M)) * sizeof(float2);
+}
+// Threads of a column-pass block: one per butterfly of the stage with the most of them, in
+// whole waves, up to 256.
+inline int col_g_threads(const FftPlan& pl) {
+  int rmin = pl.radix[0];
+  for (int i = 1; i < pl.ns; ++i) rmin = pl.radix[i] < rmin ? pl.radix[i] : rmin;
+  const int waves = (pl.L / rmin * kGW + 63) / 64;
+  return 64 * (waves < 4 ? waves : 4);
+}
+// Dynamic LDS of a column-pass block: the twiddle table, `extra` strips (the spectrum or the
+// accumulator) and the transform's buffers.
+inline size_t col_g_lds_bytes(const shs_plan* p, int extra) {
+  return (size_t(extra + col_bufs(p->pcol)) * p->n * kGW + col_tab_len(p->n)) * sizeof(float2);
 }
 // Reserves the dynamic LDS of the generic column passes for the largest supported side;
 // false if the runtime refuses.

@@ -612,17 +612,17 @@ __global__ __launch_bounds__(RowGeom<N>::THREADS) void k_row(RowParams p) {
 }
 
 // ---------------------------------------------------------------- column passes
-// Work item of a column pass: strip, a run of filters (indices into flist) whose
-// column range meets the strip, and the partial-accumulator slot (analysis; -1 when the
+// Work item of a column pass: strip, a run of entries of the work list (the filters whose
+// column range meets the strip), and the partial-accumulator slot (analysis; -1 when the
 // strip has a single item and the item finalises directly).
 struct ColParams {
   const float2* in;       // spectra read
   float2* out;            // spectra written
   const float* psiw;      // filter values inside each column window (compact)
-  const int4* pwin;       // [eta][N/2+1] {window start a, length L, value offset, 0}
+  const int4* fwin;       // per work-list entry and strip column: {window start a, length L, value offset, 0}
+  const int4* fgeo;       // per work-list entry: {cb, pitch, off_lo, off_hi} of the filter's plane
   SpecLayout tl;          // layout of the filtered spectra (compact)
-  const int4* items;      // {strip, first flist index, count, partial slot}
-  const int* flist;       // filter ids
+  const int4* items;      // {strip, first work-list entry, count, partial slot}
   const int2* strips;     // per strip {first analysis item, number of items}
   float2* part;           // partial accumulators [slot][labels][N][W]
   const float2* tw;       // exp(-2 pi i m / N)
@@ -635,21 +635,16 @@ constexpr int kItemMax = 16;   // filters per column work item
 
 // A work item's per-filter data, staged in LDS once per block: the column window of
 // every (filter, column) pair and the plane geometry {cb, pitch, off_lo, off_hi} of
-// every filter.  Without it each filter step waits on three dependent loads.
+// every filter.  Without it each filter step waits on dependent loads; the work list holds
+// the values themselves (not filter ids), so the staging is one load deep as well.
 template <int W> struct ItemStage {
   int4 win[kItemMax][W];
   int4 geo[kItemMax];
 };
-template <int N>
-__device__ __forceinline__ void stage_item(const ColParams& p, int4 it, ItemStage<ColCfg<N>::W>& st) {
-  constexpr int W = ColCfg<N>::W, M = N / 2;
-  for (int e = threadIdx.x; e < it.z * W; e += ColCfg<N>::THREADS) {
-    const int i = e / W, cc = e % W;
-    const int j = p.flist[it.y + i];
-    const int k1 = it.x * W + cc;
-    st.win[i][cc] = k1 <= M ? p.pwin[j * (M + 1) + k1] : make_int4(0, 0, 0, 0);
-    if (cc == 0) st.geo[i] = p.tl.tab[j];
-  }
+template <int W>
+__device__ __forceinline__ void stage_item(const ColParams& p, int4 it, ItemStage<W>& st, int nthr) {
+  for (int e = threadIdx.x; e < it.z * W; e += nthr) (&st.win[0][0])[e] = p.fwin[it.y * W + e];
+  for (int e = threadIdx.x; e < it.z; e += nthr) st.geo[e] = p.fgeo[it.y + e];
 }
 __device__ __forceinline__ long long geo_off(int4 g) { return (long long)(unsigned)g.z | ((long long)g.w << 32); }
 
@@ -669,13 +664,6 @@ struct PsiBuf {
     });
   }
 };
-
-// psi_j(k0, k1) from the compact window of column k1 (zero outside the window).
-template <int N>
-__device__ __forceinline__ float psi_at(const ColParams& p, int4 win, int k0) {
-  const unsigned rel = unsigned(k0 - win.x) & unsigned(N - 1);
-  return rel < unsigned(win.y) ? p.psiw[win.z + rel] : 0.f;
-}
 
 // Dense column FFT of per-label spectra: U_l = colFFT(V_l) (forward) on every column.
 template <int N>
@@ -718,7 +706,7 @@ __device__ __forceinline__ void col_syn_body(const ColParams& p, BlockId bid) {
   const bool valid = k1 <= M;
   const int l = bid.y;
   const ColAddr<W, R> A{lds + c};
-  stage_item<N>(p, it, stg);
+  stage_item(p, it, stg, G::THREADS);
   load_stage_tw_pow2<N, R, G::RM>(ctw, p.tw + col_sw_off<N>(), threadIdx.x, G::THREADS);
   cpx uh[R];
   const float2* U = p.in + l * (long long)N * p.P + (long long)it.x * (N * W) + c;
@@ -778,7 +766,7 @@ __device__ __forceinline__ void col_ana_body(const ColParams& p, BlockId bid) {
   const bool valid = k1 <= M;
   const int l = bid.y;
   const ColAddr<W, R> A{lds + c};
-  stage_item<N>(p, it, stg);
+  stage_item(p, it, stg, G::THREADS);
   load_stage_tw_pow2<N, R, G::RM>(ctw, p.tw + col_sw_off<N>(), threadIdx.x, G::THREADS);
   __syncthreads();
   // T2 column of item filter i; columns past N/2 are never written and read as zero
@@ -832,10 +820,12 @@ __device__ __forceinline__ void col_final_body(const ColParams& p, BlockId bid) 
   const ColAddr<W, R> A{lds + c};
   cpx acc[R];
   static_for<R>([&](auto r) { acc[r] = cpx{0.f, 0.f}; });
+  // a strip's partial slots are consecutive: two of them in flight at a time
+  const float2* in = p.part + ((long long)p.items[si.x].w * p.labels + l) * (N * W) + t * W + c;
+  const long long step = (long long)p.labels * (N * W);
+#pragma unroll 2
   for (int i = 0; i < si.y; ++i) {
-    const int slot = p.items[si.x + i].w;
-    const float2* in = p.part + ((long long)slot * p.labels + l) * (N * W);
-    static_for<R>([&](auto r) { acc[r] = acc[r] + ld(in + (t + r * T) * W + c); });
+    static_for<R>([&](auto r) { acc[r] = acc[r] + ld(in + i * step + r * (T * W)); });
   }
   col_finish<N>(p, acc, t, k1, valid, l, A);
 }

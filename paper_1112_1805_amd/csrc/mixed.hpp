@@ -5,33 +5,25 @@
 
 namespace shs {
 
-inline GenParams mixed_params(const shs_plan* p) { return GenParams{p->prow, p->pcol, p->n, p->wpb}; }
+inline GenParams mixed_params(const shs_plan* p) {
+  return GenParams{p->prow, p->pfwd, p->pcol, p->n, p->wpb, p->rw == 4 ? 2 : p->rw == 2 ? 1 : 0, p->nbuf};
+}
 
 template <int MODE, int ST, bool STATS>
 void mixed_row(const shs_plan* p, const RowParams& rp, int channels, hipStream_t s) {
   // p->wpb waves per block, p->rw rows per wave
   const dim3 grid(p->n / p->rpb, channels);
   const int threads = 64 * p->wpb;
-  const size_t lds = row_g_lds_bytes(p->M, p->rw, p->wpb, p->n);
+  const size_t lds = row_g_lds_bytes(p->M, p->rw, p->wpb, p->nbuf);
   if constexpr (batch_row_mode(MODE)) {
     if (g_rec) {
-      LaunchRec* r = nullptr;
-      switch (p->rw) {
-        case 4: r = &rec_add(RK_ROW, &kg_row_g<MODE, ST, STATS, 4>, threads, p->n / p->rpb, channels, lds); break;
-        case 2: r = &rec_add(RK_ROW, &kg_row_g<MODE, ST, STATS, 2>, threads, p->n / p->rpb, channels, lds); break;
-        default: r = &rec_add(RK_ROW, &kg_row_g<MODE, ST, STATS, 1>, threads, p->n / p->rpb, channels, lds); break;
-      }
-      r->rp = rp;
-      r->gp = mixed_params(p);
+      LaunchRec& r = rec_add(RK_ROW, &kg_row_g<MODE, ST, STATS>, threads, p->n / p->rpb, channels, lds);
+      r.rp = rp;
+      r.gp = mixed_params(p);
       return;
     }
   }
-  const GenParams gp = mixed_params(p);
-  switch (p->rw) {
-    case 4: hipLaunchKernelGGL((k_row_g<MODE, ST, STATS, 4>), grid, dim3(threads), lds, s, rp, gp); break;
-    case 2: hipLaunchKernelGGL((k_row_g<MODE, ST, STATS, 2>), grid, dim3(threads), lds, s, rp, gp); break;
-    default: hipLaunchKernelGGL((k_row_g<MODE, ST, STATS, 1>), grid, dim3(threads), lds, s, rp, gp); break;
-  }
+  hipLaunchKernelGGL((k_row_g<MODE, ST, STATS>), grid, dim3(threads), lds, s, rp, mixed_params(p));
 }
 
 #define SHS_MIXED_ROWS(X)                                                                    \

@@ -1,11 +1,44 @@
-// Mixed-radix column passes, the plain row transforms, and the launch table of the path.
-#include "mixed.hpp"
+// Mixed-radix forward and finishing column passes, the TV column solve, the plain row
+// transforms, and the launch table of the path.
 #include "generic_col.hpp"
 
 SHS_MIXED_ROW_HERE(ROW_C2R, ST_F32, false)
 SHS_MIXED_ROW_HERE(ROW_R2C, ST_F32, false)
+SHS_MIXED_COL_HERE(COL_FWD)
+SHS_MIXED_COL_HERE(COL_FINAL)
 
 namespace shs {
+
+SHS_MIXED_COL_EXTERN(COL_SYN)
+SHS_MIXED_COL_EXTERN(COL_ANA)
+
+static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_colg_solve(ColParams p, GenParams gp, const float* __restrict__ eig) {
+  extern __shared__ float2 gsm[];
+  const int n = gp.n, E = n * kGW, M = n / 2;
+  float2* lsw = gsm;
+  float2* bz = gsm + col_tab_len(n);
+  float2* b0 = bz + E;
+  load_table(lsw, col_sw_g(p.tw, n), n - 1);
+  const int cols = strip_cols(blockIdx.x, M);
+  const long long strip = blockIdx.y * (long long)n * p.P + (long long)blockIdx.x * E;
+  __syncthreads();
+  col_transform_g<false>(gp, lsw, b0, b0 + E, NoEarlyCol{}, StripRead{PlaneBuf(p.in + strip, E), cols >= kGW, cols},
+    [&](auto& a, int bf, int nb, int c, const auto&) {
+      constexpr int R = sizeof(a) / sizeof(cpx);
+      const float e1 = c < cols ? eig[blockIdx.x * kGW + c] : 0.f;
+      static_for<R>([&](auto k) {
+        const int pos = bf + k * nb;
+        st(bz + pos * kGW + c, a[k] * (c < cols ? p.inv_n2 / (1.f + eig[pos] + e1) : 0.f));
+      });
+    });
+  __syncthreads();
+  col_transform_g<true>(gp, lsw, b0, b0 + E, NoEarlyCol{},
+    [&](auto& a, int bf, int nb, int c) {
+      constexpr int R = sizeof(a) / sizeof(cpx);
+      static_for<R>([&](auto k) { a[k] = ld(bz + (bf + k * nb) * kGW + c); });
+    },
+    StripWrite{PlaneBuf(p.out + strip, E), cols >= kGW, cols});
+}
 
 static void mixed_row_any(const shs_plan* p, int mode, int store, bool stats, const RowParams& rp, int channels,
                           hipStream_t s) {
@@ -15,49 +48,28 @@ static void mixed_row_any(const shs_plan* p, int mode, int store, bool stats, co
 #undef SHS_CASE
 }
 
-static void mixed_col(const shs_plan* p, int kind, const ColParams& cp, int nblocks, int labels, hipStream_t s) {
-  const dim3 grid(nblocks, labels), block(256);
-  const size_t e = size_t(p->n) * kGW * sizeof(float2);
-  const size_t t = size_t(col_tab_len(p->n)) * sizeof(float2);
-  if (g_rec) {
-    LaunchRec* r = nullptr;
-    switch (kind) {
-      case 0: r = &rec_add(RK_COL, &kg_colg_fwd, 256, nblocks, labels, t + 2 * e); break;
-      case 1: r = &rec_add(RK_COL, &kg_colg_syn, 256, nblocks, labels, t + 3 * e); break;
-      case 2: r = &rec_add(RK_COL, &kg_colg_ana, 256, nblocks, labels, t + 3 * e); break;
-      case 3: r = &rec_add(RK_COL, &kg_colg_final, 256, nblocks, labels, t + 2 * e); break;
-    }
-    if (r) {
-      r->cp = cp;
-      r->gp = mixed_params(p);
-    }
-    return;
-  }
+static void mixed_col_any(const shs_plan* p, int kind, const ColParams& cp, int nblocks, int labels, hipStream_t s) {
   switch (kind) {
-    case 0: hipLaunchKernelGGL(k_colg_fwd, grid, block, t + 2 * e, s, cp, mixed_params(p)); break;
-    case 1: hipLaunchKernelGGL(k_colg_syn, grid, block, t + 3 * e, s, cp, mixed_params(p)); break;
-    case 2: hipLaunchKernelGGL(k_colg_ana, grid, block, t + 3 * e, s, cp, mixed_params(p)); break;
-    case 3: hipLaunchKernelGGL(k_colg_final, grid, block, t + 2 * e, s, cp, mixed_params(p)); break;
+    case COL_FWD: mixed_col<COL_FWD>(p, cp, nblocks, labels, s); break;
+    case COL_SYN: mixed_col<COL_SYN>(p, cp, nblocks, labels, s); break;
+    case COL_ANA: mixed_col<COL_ANA>(p, cp, nblocks, labels, s); break;
+    case COL_FINAL: mixed_col<COL_FINAL>(p, cp, nblocks, labels, s); break;
   }
 }
 
 static void mixed_col_solve(const shs_plan* p, const ColParams& cp, int labels, hipStream_t s) {
-  const size_t e = size_t(p->n) * kGW * sizeof(float2);
-  hipLaunchKernelGGL(k_colg_solve, dim3(p->NS, labels), dim3(256), 2 * e, s, cp, mixed_params(p), p->eig);
+  hipLaunchKernelGGL(k_colg_solve, dim3(p->NS, labels), dim3(col_g_threads(p->pcol)), col_g_lds_bytes(p, 1), s, cp,
+                     mixed_params(p), p->eig);
 }
 
-Ops mixed_ops() { return Ops{&mixed_row_any, &mixed_col, &mixed_col_solve}; }
+Ops mixed_ops() { return Ops{&mixed_row_any, &mixed_col_any, &mixed_col_solve}; }
 
 bool mixed_reserve_lds() {
-  const int lds3 = (3 * kGenericMaxN * kGW + col_tab_len(kGenericMaxN)) * int(sizeof(float2));
-  const int lds2 = (2 * kGenericMaxN * kGW + col_tab_len(kGenericMaxN)) * int(sizeof(float2));
-  const auto reserve = [](auto fn, int bytes) {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) ==
-           hipSuccess;
-  };
-  return reserve(&k_colg_syn, lds3) && reserve(&k_colg_ana, lds3) && reserve(&k_colg_fwd, lds2) &&
-         reserve(&k_colg_final, lds2) && reserve(&k_colg_solve, lds2) && reserve(&kg_colg_syn, lds3) &&
-         reserve(&kg_colg_ana, lds3) && reserve(&kg_colg_fwd, lds2) && reserve(&kg_colg_final, lds2);
+  const int bytes = (3 * kGenericMaxN * kGW + col_tab_len(kGenericMaxN)) * int(sizeof(float2));
+  return mixed_col_reserve<COL_FWD>() && mixed_col_reserve<COL_SYN>() && mixed_col_reserve<COL_ANA>() &&
+         mixed_col_reserve<COL_FINAL>() &&
+         hipFuncSetAttribute(reinterpret_cast<const void*>(&k_colg_solve), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             bytes) == hipSuccess;
 }
 
 }  // namespace shs

@@ -164,6 +164,31 @@ void fill_stage_tw_g(const FftPlan& pl, const std::vector<float2>& tw, int NT, f
     Ns *= R;
   }
 }
+// exp(-2 pi i m / n), m < n, from double precision.
+std::vector<float2> base_twiddles(int n) {
+  std::vector<float2> tw(n);
+  for (int m = 0; m < n; ++m) {
+    const double a = -2.0 * M_PI * double(m) / double(n);
+    tw[m] = make_float2(float(std::cos(a)), float(std::sin(a)));
+  }
+  return tw;
+}
+// The tables of a mixed-radix plan behind its base table: what a row pass copies
+// (exp(-2 pi i k / N) for k <= M = N/2, the inverse and the forward transform's stage tables
+// of M - 1 entries each, one unused entry), then the columns' stage table (N).
+void fill_stage_tables_g(const FftPlan& inv, const FftPlan& fwd, const FftPlan& col, const std::vector<float2>& tw,
+                         float2* out) {
+  const int n = col.L;
+  const int M = n / 2;
+  std::vector<float2> tab(n);
+  std::copy(tw.begin(), tw.begin() + M + 1, out);
+  fill_stage_tw_g(inv, tw, n, tab.data());
+  std::copy(tab.begin(), tab.begin() + M - 1, out + M + 1);
+  fill_stage_tw_g(fwd, tw, n, tab.data());
+  std::copy(tab.begin(), tab.begin() + M - 1, out + 2 * M);
+  out[3 * M - 1] = tw[0];
+  fill_stage_tw_g(col, tw, n, out + 3 * M);
+}
 void fill_stage_tables(int n, std::vector<float2>& tw) {
   switch (n) {
     case 64: fill_plan_tw<64>(tw); break;
@@ -212,28 +237,66 @@ Layout make_layout(const shs_plan* p) {
   return L;
 }
 
-// Stage list of a mixed-radix transform of length L (radices 16, 8, 4, 2, 9, 3 and the
-// primes 5..23); false if L has a larger prime factor.
-// Default stage list of length L: empty if L has a prime factor above 23.
-std::vector<int> fft_factors(int L) {
-  int m = L;
-  std::vector<int> rs;
-  for (int pr : {23, 19, 17, 13, 11, 7, 5}) while (m % pr == 0) { rs.push_back(pr); m /= pr; }
-  while (m % 9 == 0) { rs.push_back(9); m /= 9; }
-  while (m % 3 == 0) { rs.push_back(3); m /= 3; }
-  while (m % 16 == 0) { rs.insert(rs.begin(), 16); m /= 16; }
-  if (m == 2 || m == 4 || m == 8) { rs.insert(rs.begin(), m); m = 1; }
-  if (m != 1) rs.clear();
-  return rs;
+// Radices a stage of a mixed-radix transform can have (with_radix in generic.hpp).
+bool radix_ok(int r) {
+#define SHS_CASE(RR) if (r == RR) return true;
+  SHS_RADICES(SHS_CASE)
+#undef SHS_CASE
+  return false;
+}
+
+// Stage lists worth running for length L, best first: fewest stages (each one costs a trip
+// through LDS), then the smallest largest radix (registers, idle lanes); the two best sets
+// of radices, each in both orders.  Column transforms may also start with radix 32
+// (kFirstRadix).  Empty if L has a prime factor above 23.
+std::vector<std::vector<int>> stage_lists(int L, bool column) {
+  struct Set { std::vector<int> r; bool first; };
+  std::vector<Set> sets;
+  std::vector<int> cur;
+  for (int ns = 2; ns <= 5 && sets.empty(); ++ns) {
+    // non-increasing radix lists of ns stages with product L
+    auto rec = [&](auto&& self, int rest, int left, int most, bool first) -> void {
+      if (left == 0) {
+        if (rest == 1) sets.push_back(Set{cur, first});
+        return;
+      }
+      for (int r = most; r >= 2; --r) {
+        if (rest % r != 0 || !radix_ok(r)) continue;
+        cur.push_back(r);
+        self(self, rest / r, left - 1, r, first);
+        cur.pop_back();
+      }
+    };
+    rec(rec, L, ns, 24, false);
+    if (column && L % kFirstRadix == 0 && sets.empty()) {
+      cur.push_back(kFirstRadix);
+      rec(rec, L / kFirstRadix, ns - 1, 24, true);
+      cur.pop_back();
+    }
+  }
+  std::stable_sort(sets.begin(), sets.end(), [](const Set& a, const Set& b) {
+    return *std::max_element(a.r.begin(), a.r.end()) < *std::max_element(b.r.begin(), b.r.end());
+  });
+  if (sets.size() > 2) sets.resize(2);
+  std::vector<std::vector<int>> out;
+  for (const Set& t : sets) {
+    out.push_back(t.r);
+    std::vector<int> rev = t.r;
+    std::reverse(rev.begin() + (t.first ? 1 : 0), rev.end());
+    if (rev != t.r) out.push_back(rev);
+  }
+  return out;
 }
 
 // Plan of the stages `rs` (in this order; their product is L).
-bool fft_plan_from(int L, const std::vector<int>& rs, FftPlan& pl) {
+bool fft_plan_from(int L, const std::vector<int>& rs, FftPlan& pl, bool column) {
+  for (size_t i = 0; i < rs.size(); ++i)
+    if (!radix_ok(rs[i]) && !(column && i == 0 && rs[i] == kFirstRadix)) return false;
   pl = FftPlan{};
   pl.L = L;
   long long prod = 1;
   for (int r : rs) prod *= r;
-  if (rs.empty() || prod != L || int(rs.size()) > kMaxStages) return false;
+  if (rs.size() < 2 || prod != L || int(rs.size()) > kMaxStages) return false;
   pl.ns = int(rs.size());
   int ns = 1;
   for (int i = 0; i < pl.ns; ++i) {
@@ -249,7 +312,10 @@ bool fft_plan_from(int L, const std::vector<int>& rs, FftPlan& pl) {
   return true;
 }
 
-bool make_fft_plan(int L, FftPlan& pl) { return fft_plan_from(L, fft_factors(L), pl); }
+// The row transforms of one stage list: the inverse runs it as it is, the forward reversed.
+bool row_plans_from(int M, const std::vector<int>& rs, FftPlan& inv, FftPlan& fwd) {
+  return fft_plan_from(M, rs, inv, false) && fft_plan_from(M, std::vector<int>(rs.rbegin(), rs.rend()), fwd, false);
+}
 
 bool get_ops_pow2(int n, Ops& o);
 
@@ -327,9 +393,9 @@ ColParams col_params(const Ctx& c, int labels) {
   const shs_plan* p = c.p;
   ColParams cp{};
   cp.psiw = p->psiw;
-  cp.pwin = p->pwin;
+  cp.fwin = p->fwin;
+  cp.fgeo = p->fgeo;
   cp.tl = pruned_layout(p);
-  cp.flist = p->flist;
   cp.strips = p->strips_ana;
   cp.part = c.at<float2>(c.L.part);
   cp.tw = p->tw;
@@ -463,8 +529,8 @@ shs_status energy_of(const Ctx& c, const float* d_u, const float* d_s, double* o
 void free_plan(shs_plan* p) {
   if (!p) return;
   delete p->graphs;
-  void* bufs[] = {p->psi, p->tw, p->eig, p->psiw, p->pwin, p->tcol, p->items_syn, p->items_ana, p->flist,
-                  p->strips_ana};
+  void* bufs[] = {p->psi, p->tw, p->eig, p->psiw, p->pwin, p->tcol, p->items_syn, p->items_ana, p->fwin,
+                  p->fgeo, p->strips_ana};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete p;
@@ -567,7 +633,17 @@ shs_status build_pruned_layout(shs_plan* p, StripLists* keep) {
   if ((st = upload(&p->tcol, tcol)) != SHS_OK) return st;
   if ((st = upload(&p->items_syn, isyn)) != SHS_OK) return st;
   if ((st = upload(&p->items_ana, iana)) != SHS_OK) return st;
-  if ((st = upload(&p->flist, flist)) != SHS_OK) return st;
+  // the work list: every entry's column windows and plane geometry
+  std::vector<int4> fwin(flist.size() * W, make_int4(0, 0, 0, 0)), fgeo(flist.size());
+  for (int s = 0; s < p->NS; ++s)
+    for (size_t k = 0; k < per_strip[s].size(); ++k) {
+      const size_t e = size_t(strip_off[s]) + k;
+      const int j = per_strip[s][k];
+      fgeo[e] = tcol[j];
+      for (int c = 0; c < W && s * W + c < half; ++c) fwin[e * W + c] = pwin[size_t(j) * half + s * W + c];
+    }
+  if ((st = upload(&p->fwin, fwin)) != SHS_OK) return st;
+  if ((st = upload(&p->fgeo, fgeo)) != SHS_OK) return st;
   if ((st = upload(&p->strips_ana, strips)) != SHS_OK) return st;
   // 4. compact filter values
   if (hipMalloc(&p->psiw, size_t(std::max<long long>(off, 1)) * 4) != hipSuccess) return fail(SHS_E_NOMEM, "psiw");
@@ -920,9 +996,8 @@ void build_batch_iter(const std::vector<LaunchRec>& recs, std::vector<char>& are
 // takes its largest image's LDS, so only images of one occupancy share a launch).
 int batch_class(const shs_plan* p) {
   if (!p->generic) return p->n;
-  const int lds3 = (3 * p->n * kGW + col_tab_len(p->n)) * int(sizeof(float2));
-  const int bpc = std::min(4, (160 * 1024) / lds3);
-  return 100000 + p->wpb * 100 + p->rw * 10 + bpc;
+  const int bpc = std::min(6, int(160 * 1024 / col_g_lds_bytes(p, 1)));
+  return 100000 + (col_g_threads(p->pcol) / 64) * 1000 + p->wpb * 100 + p->rw * 10 + bpc;
 }
 
 void launch_batch_iter(const BatchIter& iter, char* dbase, hipStream_t s) {
@@ -1009,46 +1084,24 @@ void tune_cache_store(const std::string& key, const TuneCfg& c) {
   }
 }
 
-// Stage orders worth timing: the default, reversed, radix 16 as 4 x 4, powers of two last.
-std::vector<std::vector<int>> order_candidates(const std::vector<int>& d) {
-  std::vector<std::vector<int>> out{d};
-  auto add = [&](const std::vector<int>& v) {
-    if (int(v.size()) <= kMaxStages && std::find(out.begin(), out.end(), v) == out.end()) out.push_back(v);
-  };
-  add(std::vector<int>(d.rbegin(), d.rend()));
-  std::vector<int> split;
-  for (int r : d) {
-    if (r == 16) { split.push_back(4); split.push_back(4); }
-    else split.push_back(r);
-  }
-  add(split);
-  std::vector<int> odd_first;
-  for (int r : d) if (r & 1) odd_first.push_back(r);
-  for (int r : d) if (!(r & 1)) odd_first.push_back(r);
-  add(odd_first);
-  return out;
-}
-
 // Installs a schedule in the plan: FFT plans and their twiddle tables, rows per wave, and
 // the synthesis work items.
 shs_status apply_schedule(shs_plan* p, const TuneCfg& c, const StripLists& sl) {
-  FftPlan pr, pc;
-  if (!fft_plan_from(p->M, c.prow, pr) || !fft_plan_from(p->n, c.pcol, pc)) return fail(SHS_E_DEVICE, "bad schedule");
+  FftPlan pr, pf, pc;
+  if (!row_plans_from(p->M, c.prow, pr, pf) || !fft_plan_from(p->n, c.pcol, pc, true))
+    return fail(SHS_E_DEVICE, "bad schedule");
   const int n = p->n;
-  std::vector<float2> tw(n);
-  for (int m = 0; m < n; ++m) {
-    const double a = -2.0 * M_PI * double(m) / double(n);
-    tw[m] = make_float2(float(std::cos(a)), float(std::sin(a)));
-  }
-  std::vector<float2> tabs(size_t(n) / 2 + n);
-  fill_stage_tw_g(pr, tw, n, tabs.data());
-  fill_stage_tw_g(pc, tw, n, tabs.data() + n / 2);
+  const std::vector<float2> tw = base_twiddles(n);
+  std::vector<float2> tabs(size_t(n) / 2 * 3 + n);
+  fill_stage_tables_g(pr, pf, pc, tw, tabs.data());
   HIPCHK(hipMemcpy(p->tw + n, tabs.data(), tabs.size() * sizeof(float2), hipMemcpyHostToDevice));
   p->prow = pr;
+  p->pfwd = pf;
   p->pcol = pc;
   p->rw = c.rw;
   p->wpb = c.wpb;
   p->rpb = c.wpb * c.rw;
+  p->nbuf = row_g_bufs(pr, c.rw);
   if (c.fc_syn != p->fc_syn) {
     std::vector<int4> isyn;
     build_items(sl.per_strip, sl.strip_off, c.fc_syn, false, isyn, nullptr, nullptr);
@@ -1075,8 +1128,9 @@ shs_status tune_schedule(shs_plan* p, const StripLists& sl) {
   base.rw = p->rw;
   base.wpb = p->wpb;
   base.fc_syn = p->fc_syn;
-  base.prow = fft_factors(p->M);
-  base.pcol = fft_factors(p->n);
+  const std::vector<std::vector<int>> row_lists = stage_lists(p->M, false), col_lists = stage_lists(p->n, true);
+  base.prow = row_lists[0];
+  base.pcol = col_lists[0];
   for (auto& e : g_tune)
     if (e.first == key) {
       const shs_status st = apply_schedule(p, e.second, sl);
@@ -1135,9 +1189,12 @@ shs_status tune_schedule(shs_plan* p, const StripLists& sl) {
    for (int wpb : {4, 2, 1}) {
     // a block's rows divide N and its LDS stays within the limit; one wave per block only
     // where four rows per wave would not otherwise fit
-    if (p->n % (rw * wpb) != 0 || row_g_lds_bytes(p->M, rw, wpb, p->n) > kRowGLdsMax) continue;
-    if (wpb == 1 && rw < 4) continue;
-    for (const auto& ord : order_candidates(base.prow)) {
+    if (p->n % (rw * wpb) != 0 || (wpb == 1 && rw < 4)) continue;
+    for (const auto& ord : row_lists) {
+      FftPlan pr, pf;
+      if (!row_plans_from(p->M, ord, pr, pf) ||
+          row_g_lds_bytes(p->M, rw, wpb, row_g_bufs(pr, rw)) > kRowGLdsMax)
+        continue;
       TuneCfg c = best;
       c.rw = rw;
       c.wpb = wpb;
@@ -1162,7 +1219,7 @@ shs_status tune_schedule(shs_plan* p, const StripLists& sl) {
   float best_col = 1e30f;
   std::vector<int> fcs;
   for (int fc : {1, 2, 4, 8, 16}) if (fc <= kItemMax) fcs.push_back(fc);
-  for (const auto& ord : order_candidates(base.pcol)) {
+  for (const auto& ord : col_lists) {
     for (int fc : fcs) {
       TuneCfg c = best;
       c.pcol = ord;
@@ -1386,11 +1443,13 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
     return fail(SHS_E_INVALID, "J must satisfy J >= 1 and 4^J <= 2N");
   if (shape->store < SHS_STORE_F32 || shape->store > SHS_STORE_F16) return fail(SHS_E_INVALID, "bad store type");
   Ops o;
-  FftPlan prow{}, pcol{};
+  FftPlan prow{}, pfwd{}, pcol{};
   const bool pow2 = get_ops_pow2(n, o);
   if (!pow2) {
     // mixed-radix path: N a multiple of 8 in [64, 1024] whose prime factors are <= 23
-    if (n % 8 != 0 || n < 64 || n > kGenericMaxN || !make_fft_plan(n / 2, prow) || !make_fft_plan(n, pcol))
+    const auto rows = stage_lists(n / 2, false), cols = stage_lists(n, true);
+    if (n % 8 != 0 || n < 64 || n > kGenericMaxN || rows.empty() || cols.empty() ||
+        !row_plans_from(n / 2, rows[0], prow, pfwd) || !fft_plan_from(n, cols[0], pcol, true))
       return fail(SHS_E_UNSUPPORTED,
                   "n must be a power of two in 64..2048 or a multiple of 8 in 64..1024 with prime factors <= 23");
   }
@@ -1409,12 +1468,15 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
   p->M = n / 2;
   p->generic = pow2 ? 0 : 1;
   p->prow = prow;
+  p->pfwd = pfwd;
   p->pcol = pcol;
   p->W = pow2 ? by_size<WOf>(n) : kGW;
-  // generic rows: several rows per wave keep the lanes busy in stages with few butterflies;
-  // the two LDS buffers of a block (4 waves, 64 M rw bytes) stay at or below 48 KB, beside
-  // the 8 N bytes of twiddle tables
-  p->rw = pow2 ? 1 : (n % 16 == 0 && p->M <= 192) ? 4 : (p->M <= 384 ? 2 : 1);
+  // generic rows: as many rows per wave (up to 4, in blocks that divide N) as keep every
+  // stage one pass over the wave's lanes
+  p->rw = 1;
+  if (!pow2)
+    while (p->rw < 4 && n % (8 * p->rw) == 0 && row_g_bufs(prow, 2 * p->rw) == 1) p->rw *= 2;
+  p->nbuf = pow2 ? 0 : row_g_bufs(prow, p->rw);
   p->wpb = 4;
   p->rpb = pow2 ? by_size<RpbOf>(n) : p->wpb * p->rw;
   p->NS = p->M / p->W + 1;
@@ -1423,18 +1485,14 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
   p->device = device;
   const size_t psi_bytes = size_t(p->eta) * n * p->PP * 4;
   if (hipMalloc(&p->psi, psi_bytes) != hipSuccess) { free_plan(p); return fail(SHS_E_NOMEM, "filter bank allocation"); }
-  std::vector<float2> tw(n);
-  for (int m = 0; m < n; ++m) {
-    const double a = -2.0 * M_PI * double(m) / double(n);
-    tw[m] = make_float2(float(std::cos(a)), float(std::sin(a)));
-  }
+  std::vector<float2> tw = base_twiddles(n);
   // append the row and column stage tables
   if (pow2) {
     fill_stage_tables(n, tw);
   } else {
-    tw.resize(size_t(n) + n / 2 + n);
-    fill_stage_tw_g(prow, tw, n, tw.data() + n);
-    fill_stage_tw_g(pcol, tw, n, tw.data() + n + n / 2);
+    const std::vector<float2> base = tw;
+    tw.resize(size_t(n) + n / 2 * 3 + n);
+    fill_stage_tables_g(p->prow, p->pfwd, p->pcol, base, tw.data() + n);
   }
   if (hipMalloc(&p->tw, tw.size() * 8) != hipSuccess) { free_plan(p); return fail(SHS_E_NOMEM, "twiddle allocation"); }
   std::vector<float> eig(n);
