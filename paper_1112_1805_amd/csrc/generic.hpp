@@ -23,6 +23,7 @@ struct FftPlan {
   unsigned mag[kMaxStages];
   int sh[kMaxStages];
 };
+using PlanRef = const __attribute__((address_space(4))) FftPlan*;   // in constant memory
 // LDS buffers of one strip a column transform needs between its stages.
 inline int col_bufs(const FftPlan& pl) { return pl.ns > 2 ? 2 : 1; }
 
@@ -133,8 +134,8 @@ struct StageGeom {
   unsigned mag;
   int sh;
 };
-__device__ __forceinline__ StageGeom stage_geom(const FftPlan& pl, int s, int Ns) {
-  return StageGeom{pl.L, Ns, pl.mag[s], pl.sh[s]};
+__device__ __forceinline__ StageGeom stage_geom(PlanRef pl, int s, int Ns) {
+  return StageGeom{pl->L, Ns, pl->mag[s], pl->sh[s]};
 }
 // What `early` loaded, or (EARLY = false) what `now` loads.
 template <bool EARLY, class E, class F>
@@ -196,10 +197,10 @@ struct LdsWrite {
 // buffer that holds the result (alt == cur is allowed where every stage is one pass of one
 // wave, whose reads all precede its writes).  Ns: stride of stage s0 on entry, of s1 on exit.
 template <bool INV, int SK>
-__device__ __forceinline__ float2* gfft_stages(const FftPlan& pl, int s0, int s1, int& Ns, float2* cur, float2* alt,
+__device__ __forceinline__ float2* gfft_stages(PlanRef pl, int s0, int s1, int& Ns, float2* cur, float2* alt,
                                                int lw, int nthr, int tid, const float2* sw) {
   for (int s = s0; s < s1; ++s) {
-    const int r = pl.radix[s];
+    const int r = pl->radix[s];
     const StageGeom q = stage_geom(pl, s, Ns);
     with_radix(r, [&](auto R) __attribute__((always_inline)) {
       gstage<R, INV>(q, lw, nthr, tid, sw, NoEarly{}, LdsRead{cur, lw}, LdsWrite{alt, lw, q.Ns});
@@ -217,14 +218,21 @@ __device__ __forceinline__ float2* gfft_stages(const FftPlan& pl, int s0, int s1
 constexpr int kGW = 4;          // strip width of the generic path
 constexpr int kGLW = 2;         // its logarithm
 
+// The launch parameters of the path.  The stage lists stay in device memory and are read
+// through constant-memory (scalar) loads: they are indexed by a runtime stage number, for which
+// the compiler would copy a by-value kernel argument to scratch memory and read it back from
+// there before every stage (middle step at 360^2, q = 2: 37 us against 21 us).
+enum { FFT_INV = 0, FFT_FWD = 1, FFT_COL = 2 };   // inverse rows, forward rows (reversed), columns
 struct GenParams {
-  FftPlan pinv;   // inverse row transform, length N/2
-  FftPlan pfwd;   // forward row transform: the same stages in reverse order
-  FftPlan pcol;   // column transforms, length N
+  const FftPlan* plans;   // [3]
   int n;
   int wpb;        // waves per row-pass block (1, 2 or 4; the block is 64 wpb threads)
   int lrw;        // log2 of the rows per wave
   int nbuf;       // LDS buffers per row-pass wave: 1 where every stage is one pass, else 2
+  int lrb;        // middle step: log2 of the rows per block
+  __device__ __forceinline__ PlanRef inv() const { return (PlanRef)(plans + FFT_INV); }
+  __device__ __forceinline__ PlanRef fwd() const { return (PlanRef)(plans + FFT_FWD); }
+  __device__ __forceinline__ PlanRef col() const { return (PlanRef)(plans + FFT_COL); }
 };
 // Twiddle table of a mixed-radix plan, one device array: [0, N) exp(-2 pi i m / N); then what
 // a row pass copies, 3 N/2 entries (see row_tab_len); then the column transform's stage table
@@ -264,6 +272,57 @@ __device__ __forceinline__ int tix_g(int ip, int row, int n) {
   return (ip >> 2) * (n * kGW) + row * kGW + (ip & (kGW - 1));     // floor for negative ip
 }
 
+// Inputs of a butterfly of the inverse row transform's first stage from a half spectrum:
+// z[k] = s + i d W_N^{-k} with s = X[k] + conj(X[M-k]), d = X[k] - conj(X[M-k]), k = bf + i nb.
+// load(k) returns X[k]; only the columns [cb, cb + pitch) exist, and whole chunks [i nb, i nb +
+// nb) that miss them directly or mirrored are skipped.
+template <int R, class Load>
+__device__ __forceinline__ void real_pre(cpx (&a)[R], int bf, int nb, int M, int cb, int pitch, const float2* ltw,
+                                         Load&& load) {
+  const auto in_p = [&](int k0) { return k0 < cb + pitch && k0 + nb > cb; };
+  const auto in_m = [&](int k0) { return k0 <= M - cb && k0 + nb > M - cb - pitch; };
+  // in groups of 8 bins: their mirrored bins' registers bound the butterfly's footprint
+  constexpr int H = 8;
+  static_for<(R + H - 1) / H>([&](auto h) {
+    constexpr int i0 = h * H, cnt = R - i0 < H ? R - i0 : H;
+    cpx xm[H];
+    static_for<cnt>([&](auto m) {
+      constexpr int i = i0 + m;
+      const int k = bf + i * nb;
+      a[i] = cpx{0.f, 0.f};
+      xm[m] = cpx{0.f, 0.f};
+      if (in_p(i * nb)) a[i] = load(k);
+      if (in_m(i * nb)) xm[m] = load(M - k);
+    });
+    static_for<cnt>([&](auto m) {
+      constexpr int i = i0 + m;
+      if (in_p(i * nb) || in_m(i * nb)) {
+        const cpx s = a[i] + conj(xm[m]), d = a[i] - conj(xm[m]);
+        const cpx w = ld(ltw + (bf + i * nb));   // W_N^k
+        a[i] = cpx{fmaf(d.x, w.y, fmaf(-d.y, w.x, s.x)), fmaf(d.x, w.x, fmaf(d.y, w.y, s.y))};
+      }
+    });
+  });
+}
+// Half spectra of the 2^lw rows whose forward transforms Y sit interleaved in LDS: bins k and
+// M - k come from the same two points, X[k] = (s - i d W^k) / 2 and X[M-k] = conj(s + i d W^k) / 2
+// with s = Y[k] + conj(Y[M-k]), d = Y[k] - conj(Y[M-k]).  hs: 1/2, or 1 where the rows were passed
+// in halved.  store(c, k, x) takes bin k of row c.
+template <class Store>
+__device__ __forceinline__ void real_post(const float2* Y, int M, int lw, int lane, const float2* ltw, float hs,
+                                          Store&& store) {
+  const int items = (M / 2 + 1) << lw;
+  for (int it = lane; it < items; it += 64) {
+    const int c = it & ((1 << lw) - 1), k = it >> lw;
+    const cpx yk = ld(Y + it);
+    const cpx ym = conj(ld(Y + (((k == 0 ? 0 : M - k) << lw) + c)));
+    const cpx s = yk + ym, d = yk - ym;
+    const cpx e = mul_i(cmul(d, ld(ltw + k)));
+    store(c, k, (s - e) * hs);
+    store(c, M - k, conj(s + e) * hs);
+  }
+}
+
 template <class Pair, int R> struct StatePairs { Pair v[R]; };
 
 template <int MODE, int ST, bool STATS>
@@ -278,7 +337,7 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
   const int row0 = (bid.x * gp.wpb + wave) << lw;
   const int ch = bid.y;
   const int j = ch % p.eta;
-  const int last = gp.pinv.ns - 1;
+  const int last = gp.inv()->ns - 1;
   float2* ltw = gsm;                     // exp(-2 pi i k / N), k <= M
   float2* isw = gsm + M + 1;             // inverse row transform's stage table
   float2* fsw = isw + M - 1;             // forward row transform's
@@ -299,44 +358,19 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
     long long off;
     plane_geom(p.lin, ch % p.lin.nf, cb, pitch, off);
     const PlaneBuf B(p.spec_in + (ch / p.lin.nf) * p.lin.ls + off, pitch * n);
-    // first stage: z[k] = s + i d W_N^{-k} with s = X[k] + conj(X[M-k]), d = X[k] - conj(X[M-k]);
-    // bins outside the plane's columns are out-of-range buffer loads (zero), and whole chunks
-    // [i nb, i nb + nb) that miss the window directly or mirrored are skipped
-    with_radix(gp.pinv.radix[0], [&](auto R) __attribute__((always_inline)) {
-      gstage<R, true>(stage_geom(gp.pinv, 0, 1), lw, 64, lane, isw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
-        const auto in_p = [&](int k0) { return k0 < cb + pitch && k0 + nb > cb; };
-        const auto in_m = [&](int k0) { return k0 <= M - cb && k0 + nb > M - cb - pitch; };
-        // in groups of 8 bins: their mirrored bins' registers bound the butterfly's footprint
-        constexpr int H = 8;
-        static_for<(R + H - 1) / H>([&](auto h) {
-          constexpr int i0 = h * H, cnt = R - i0 < H ? R - i0 : H;
-          cpx xm[H];
-          static_for<cnt>([&](auto m) {
-            constexpr int i = i0 + m;
-            const int k = bf + i * nb;
-            a[i] = cpx{0.f, 0.f};
-            xm[m] = cpx{0.f, 0.f};
-            if (in_p(i * nb)) a[i] = B.load(tix_g(k - cb, row0 + c, n));
-            if (in_m(i * nb)) xm[m] = B.load(tix_g(M - k - cb, row0 + c, n));
-          });
-          static_for<cnt>([&](auto m) {
-            constexpr int i = i0 + m;
-            if (in_p(i * nb) || in_m(i * nb)) {
-              const cpx s = a[i] + conj(xm[m]), d = a[i] - conj(xm[m]);
-              const cpx w = ld(ltw + (bf + i * nb));   // W_N^k
-              a[i] = cpx{fmaf(d.x, w.y, fmaf(-d.y, w.x, s.x)), fmaf(d.x, w.x, fmaf(d.y, w.y, s.y))};
-            }
-          });
-        });
+    // first stage (bins outside the plane's columns are out-of-range buffer loads: zero)
+    with_radix(gp.inv()->radix[0], [&](auto R) __attribute__((always_inline)) {
+      gstage<R, true>(stage_geom(gp.inv(), 0, 1), lw, 64, lane, isw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
+        real_pre(a, bf, nb, M, cb, pitch, ltw, [&](int k) { return B.load(tix_g(k - cb, row0 + c, n)); });
       }, LdsWrite{cur, lw, 1});
     });
     fft_sync<SYNC_WAVE>();
-    int Ns = gp.pinv.radix[0];
-    float2* res = gfft_stages<true, SYNC_WAVE>(gp.pinv, 1, last, Ns, cur, alt, lw, 64, lane, isw);
+    int Ns = gp.inv()->radix[0];
+    float2* res = gfft_stages<true, SYNC_WAVE>(gp.inv(), 1, last, Ns, cur, alt, lw, 64, lane, isw);
     alt = res == cur ? alt : cur;
     cur = res;
     // last stage, update, and the forward transform's first stage
-    with_radix(gp.pinv.radix[last], [&](auto R) __attribute__((always_inline)) {
+    with_radix(gp.inv()->radix[last], [&](auto R) __attribute__((always_inline)) {
       const int nb = M / R;
       // the state's pairs: loaded before the butterfly where its registers allow, else after it
       constexpr bool STATE = MODE == ROW_SOLVE || MODE == ROW_PD;
@@ -344,14 +378,17 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
       const auto load_state = [&](int bf, int c) {
         StatePairs<typename S::Pair, STATE ? int(R) : 1> e;
         const typename S::T* g = state(c);
-        static_for<R>([&](auto i) { e.v[i] = S::load_pair(g + 2 * (bf + i * nb)); });
+        static_for<R>([&](auto i) {
+          e.v[i] = typename S::Pair{};
+          if (!p.fresh) e.v[i] = S::load_pair(g + 2 * (bf + i * nb));
+        });
         return e;
       };
       const auto early = [&](int bf, int c) {
         if constexpr (EARLY) return load_state(bf, c);
         else return 0;
       };
-      gstage<R, true>(stage_geom(gp.pinv, last, Ns), lw, 64, lane, isw, early, LdsRead{cur, lw},
+      gstage<R, true>(stage_geom(gp.inv(), last, Ns), lw, 64, lane, isw, early, LdsRead{cur, lw},
                       [&](cpx (&a)[R], int, int bf, int c, const auto& e0) {
         if constexpr (MODE == ROW_C2R) {
           float* out = p.real_out + ch * p.real_cs + (long long)(row0 + c) * n;
@@ -424,8 +461,8 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
   }
   if constexpr (MODE == ROW_C2R) return;
   if constexpr (MODE == ROW_R2C || MODE == ROW_PRIME) {
-    with_radix(gp.pfwd.radix[0], [&](auto R) __attribute__((always_inline)) {
-      gstage<R, false>(stage_geom(gp.pfwd, 0, 1), lw, 64, lane, fsw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
+    with_radix(gp.fwd()->radix[0], [&](auto R) __attribute__((always_inline)) {
+      gstage<R, false>(stage_geom(gp.fwd(), 0, 1), lw, 64, lane, fsw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
         if constexpr (MODE == ROW_R2C) {
           const float* in = p.real_in + ch * p.real_cs + (long long)(row0 + c) * n;
           static_for<R>([&](auto i) { a[i] = ld(reinterpret_cast<const float2*>(in + 2 * (bf + i * nb))); });
@@ -443,26 +480,15 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
   if constexpr (MODE != ROW_ENERGY) {
     if (emit) {
       fft_sync<SYNC_WAVE>();
-      int Ns = gp.pfwd.radix[0];
-      const float2* Y = gfft_stages<false, SYNC_WAVE>(gp.pfwd, 1, last + 1, Ns, alt, cur, lw, 64, lane, fsw);
+      int Ns = gp.fwd()->radix[0];
+      const float2* Y = gfft_stages<false, SYNC_WAVE>(gp.fwd(), 1, last + 1, Ns, alt, cur, lw, 64, lane, fsw);
       int cb, pitch;
       long long off;
       plane_geom(p.lout, ch % p.lout.nf, cb, pitch, off);
       const PlaneBuf B(p.spec_out + (ch / p.lout.nf) * p.lout.ls + off, pitch * n);
-      // bins k and M - k of a row come from the same two points: X[k] = (s - i d W^k) / 2 and
-      // X[M-k] = conj(s + i d W^k) / 2 with s = Y[k] + conj(Y[M-k]), d = Y[k] - conj(Y[M-k]);
-      // stores outside the plane's columns are dropped (out-of-range buffer stores)
-      const float hs = HALVED ? 1.f : 0.5f;
-      const int items = (M / 2 + 1) << lw;
-      for (int it = lane; it < items; it += 64) {
-        const int c = it & ((1 << lw) - 1), k = it >> lw, row = row0 + c;
-        const cpx yk = ld(Y + it);
-        const cpx ym = conj(ld(Y + (((k == 0 ? 0 : M - k) << lw) + c)));
-        const cpx s = yk + ym, d = yk - ym;
-        const cpx e = mul_i(cmul(d, ld(ltw + k)));
-        B.store(tix_g(k - cb, row, n), (s - e) * hs);
-        B.store(tix_g(M - k - cb, row, n), conj(s + e) * hs);
-      }
+      real_post(Y, M, lw, lane, ltw, HALVED ? 1.f : 0.5f, [&](int c, int k, cpx x) {
+        B.store(tix_g(k - cb, row0 + c, n), x);      // outside the plane's columns: dropped
+      });
     }
   }
   if constexpr (STATS) {
@@ -479,6 +505,70 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
 template <int MODE, int ST, bool STATS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_row_g(RowParams p, GenParams gp) {
   row_g_body<MODE, ST, STATS>(p, gp, own_block());
+}
+
+// ---------------------------------------------------------------- generic middle step
+// As mid_body: slot l RB + r is row r of label l, a wave transforms 2^lrw slots at a time.
+// Dynamic LDS: the twiddle tables, the slots' rows (2^lrw interleaved), and with two buffers
+// one more per wave.
+template <int MODE, bool STATS>
+__device__ __forceinline__ void mid_g_body(const MidParams& p, const GenParams& gp, BlockId bid) {
+  extern __shared__ float2 gsm[];
+  __shared__ double red[16 * 4];
+  const int n = gp.n, M = n / 2, lw = gp.lrw, lrb = gp.lrb, RB = 1 << lrb;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int row0 = xcd_chunked(bid.x, bid.gx) * RB, groups = (RB * p.q) >> lw;
+  float2* ltw = gsm;                     // as in the row pass
+  float2* isw = gsm + M + 1;
+  float2* fsw = isw + M - 1;
+  float2* res = gsm + row_tab_len(n);
+  float2* alt = res + ((groups * M) << lw) + ((wave * M) << lw);   // two buffers only
+  load_table(ltw, row_sw_g(p.tw, n), 3 * M - 1);
+  __syncthreads();
+  if (p.z) {
+    const PlaneBuf B(p.z, p.q * n * p.P);
+    for (int g = wave; g < groups; g += nw) {
+      float2* r = res + ((g * M) << lw);
+      // the transform's result lands in r: start there or in the second buffer by its parity
+      float2* a0 = gp.nbuf == 1 || gp.inv()->ns % 2 == 1 ? r : alt;
+      float2* a1 = gp.nbuf == 1 ? r : (a0 == r ? alt : r);
+      with_radix(gp.inv()->radix[0], [&](auto R) __attribute__((always_inline)) {
+        gstage<R, true>(stage_geom(gp.inv(), 0, 1), lw, 64, lane, isw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
+          const int s = (g << lw) + c, l = s >> lrb;
+          const int base = l * n * p.P, row = row0 + (s & (RB - 1));
+          real_pre(a, bf, nb, M, 0, p.P, ltw, [&](int k) { return B.load(base + tix_g(k, row, n)); });
+        }, LdsWrite{a0, lw, 1});
+      });
+      fft_sync<SYNC_WAVE>();
+      int Ns = gp.inv()->radix[0];
+      gfft_stages<true, SYNC_WAVE>(gp.inv(), 1, gp.inv()->ns, Ns, a0, a1, lw, 64, lane, isw);
+    }
+  }
+  __syncthreads();
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  pixel_rows_q<MODE, STATS>(p, row0, RB, n, blockDim.x, acc, [&](int l, int r, int k) {
+    const int s = (l << lrb) + r;
+    return res + ((((s >> lw) * M + k) << lw) + (s & ((1 << lw) - 1)));
+  });
+  __syncthreads();
+  if (p.emit) {
+    const PlaneBuf B(p.v, p.q * n * p.P);
+    for (int g = wave; g < groups; g += nw) {
+      float2* r = res + ((g * M) << lw);
+      int Ns = 1;
+      const float2* Y = gfft_stages<false, SYNC_WAVE>(gp.fwd(), 0, gp.fwd()->ns, Ns, r, gp.nbuf == 1 ? r : alt, lw, 64, lane, fsw);
+      real_post(Y, M, lw, lane, ltw, 0.5f, [&](int c, int k, cpx x) {
+        const int s = (g << lw) + c, l = s >> lrb;
+        B.store(l * n * p.P + tix_g(k, row0 + (s & (RB - 1)), n), x);
+      });
+      fft_sync<SYNC_WAVE>();   // the next group's second buffer is this one's
+    }
+  }
+  if constexpr (STATS) mid_partials(p, acc, red, nw, bid);
+}
+template <int MODE, bool STATS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_mid_g(MidParams p, GenParams gp) {
+  mid_g_body<MODE, STATS>(p, gp, own_block());
 }
 
 }  // namespace shs

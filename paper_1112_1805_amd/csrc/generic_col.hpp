@@ -42,18 +42,18 @@ struct NoEarlyCol {
 template <bool INV, class Early, class Load, class Done>
 __device__ __forceinline__ void col_transform_g(const GenParams& gp, const float2* lsw, float2* b0, float2* b1,
                                                 Early&& early, Load&& load, Done&& done) {
-  const FftPlan& pl = gp.pcol;
-  const int last = pl.ns - 1, nthr = blockDim.x, tid = threadIdx.x;
+  const PlanRef pl = gp.col();
+  const int last = pl->ns - 1, nthr = blockDim.x, tid = threadIdx.x;
   const auto first = [&](auto R) __attribute__((always_inline)) {
     gstage<R, INV>(stage_geom(pl, 0, 1), kGLW, nthr, tid, lsw, NoEarly{}, load, LdsWrite{b0, kGLW, 1});
   };
-  if (pl.radix[0] == kFirstRadix) first(std::integral_constant<int, kFirstRadix>{});
-  else with_radix(pl.radix[0], first);
+  if (pl->radix[0] == kFirstRadix) first(std::integral_constant<int, kFirstRadix>{});
+  else with_radix(pl->radix[0], first);
   __syncthreads();
-  int Ns = pl.radix[0];
+  int Ns = pl->radix[0];
   const float2* cur = gfft_stages<INV, SYNC_BLOCK>(pl, 1, last, Ns, b0, b1, kGLW, nthr, tid, lsw);
-  with_radix(pl.radix[last], [&](auto R) __attribute__((always_inline)) {
-    const int nb = pl.L / R;
+  with_radix(pl->radix[last], [&](auto R) __attribute__((always_inline)) {
+    const int nb = pl->L / R;
     gstage<R, INV>(stage_geom(pl, last, Ns), kGLW, nthr, tid, lsw,
                    [&](int bf, int c) { return early(R, bf, nb, c); }, LdsRead{cur, kGLW},
                    [&](cpx (&a)[R], int, int bf, int c, const auto& e) { done(a, bf, nb, c, e); });

@@ -68,6 +68,13 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS) __attribute__((amdgpu_waves_per
   col_final_body<N>(T.p, group_block(T));
 }
 
+template <int N, bool STATS>
+__global__ __launch_bounds__(64 * MidGeom<N>::waves(8)) void kg_mid(const GroupTask<MidParams>* __restrict__ tasks,
+                                                                    const uint16_t* __restrict__ bt) {
+  const GroupTask<MidParams>& T = group_task(tasks, bt);
+  mid_body<N, MID_ADMM, STATS>(T.p, group_block(T));
+}
+
 // ---- mixed-radix sizes (runtime N; dynamic LDS sized for the group's largest image)
 template <int MODE, int ST, bool STATS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void kg_row_g(const GroupTask<RowParams>* __restrict__ tasks,
@@ -75,13 +82,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const GroupTask<RowParams>& T = group_task(tasks, bt);
   row_g_body<MODE, ST, STATS>(T.p, T.gp, group_block(T));
 }
-
-// ---- pixel step (any size)
-template <bool STATS, bool HAVE_Z>
-__global__ __launch_bounds__(256) void kg_pixel(const GroupTask<PixParams>* __restrict__ tasks,
-                                                const uint16_t* __restrict__ bt) {
-  const GroupTask<PixParams>& T = group_task(tasks, bt);
-  pixel_body<STATS, HAVE_Z>(T.p, group_block(T));
+template <int MODE, bool STATS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void kg_mid_g(
+    const GroupTask<MidParams>* __restrict__ tasks, const uint16_t* __restrict__ bt) {
+  const GroupTask<MidParams>& T = group_task(tasks, bt);
+  mid_g_body<MODE, STATS>(T.p, T.gp, group_block(T));
 }
 
 }  // namespace shs

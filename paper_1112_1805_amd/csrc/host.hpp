@@ -21,6 +21,7 @@ struct shs_plan {
   int wpb;             // generic path: waves per row-pass block (1, 2 or 4)
   int nbuf;            // generic path: LDS buffers per row-pass wave (row_g_bufs)
   FftPlan prow, pfwd, pcol;  // mixed-radix transforms: inverse rows, forward rows, columns
+  FftPlan* fft;        // the same three in device memory (FFT_* order)
   float* psi;          // [eta][N][PP] dense filter bank (half spectrum)
   float2* tw;          // [N] exp(-2 pi i m / N), then (power-of-two N) the FFT stage tables
   float* eig;          // [N] 4 sin^2(pi k / N): DFT eigenvalues of one forward-difference pair (TV)
@@ -69,8 +70,8 @@ namespace shs {
 // each launch, with the grouped kernel of its configuration, instead of launching; the
 // batch solve turns one iteration's records of all images into grouped launches.  Each
 // record carries the step of the iteration it belongs to.
-enum BatchStep { BS_ANA, BS_FINAL, BS_C2R, BS_PIXEL, BS_R2C, BS_FWD, BS_SYN, BS_ROW, BS_REDUCE, BS_COUNT };
-enum RecKind { RK_ROW, RK_COL, RK_PIX, RK_REDUCE };
+enum BatchStep { BS_ANA, BS_FINAL, BS_MID, BS_FWD, BS_SYN, BS_ROW, BS_REDUCE, BS_COUNT };
+enum RecKind { RK_ROW, RK_COL, RK_MID, RK_REDUCE };
 struct LaunchRec {
   int step = 0, kind = 0;
   const void* fn = nullptr;    // grouped kernel of the launch's configuration
@@ -78,7 +79,7 @@ struct LaunchRec {
   size_t lds = 0;              // dynamic LDS bytes
   RowParams rp{};
   ColParams cp{};
-  PixParams pp{};
+  MidParams mp{};
   GenParams gp{};
   // RK_REDUCE (one image's two-level FP64 reduction)
   double* parts = nullptr;
@@ -96,7 +97,7 @@ inline void rec_step(int s) {
   if (g_rec) g_rec->step = s;
 }
 // Row-pass modes of a batch's iterations (the others have no grouped kernel).
-constexpr bool batch_row_mode(int mode) { return mode == ROW_SOLVE || mode == ROW_C2R || mode == ROW_R2C; }
+constexpr bool batch_row_mode(int mode) { return mode == ROW_SOLVE; }
 template <class F>
 LaunchRec& rec_add(int kind, F fn, int threads, int gx, int gy, size_t lds) {
   LaunchRec r;
@@ -117,6 +118,10 @@ struct Ops {
   void (*row)(const shs_plan*, int, int, bool, const RowParams&, int, hipStream_t);
   void (*col)(const shs_plan*, int, const ColParams&, int, int, hipStream_t);
   void (*col_solve)(const shs_plan*, const ColParams&, int, hipStream_t);
+  // middle step (MID_*) and its blocks
+  void (*mid)(const shs_plan*, int, const MidParams&, hipStream_t);
+  int (*mid_blocks)(const shs_plan*);
+  bool (*reserve)();   // dynamic LDS beyond the default limit; false if the runtime refuses
 };
 enum { COL_FWD = 0, COL_SYN = 1, COL_ANA = 2, COL_FINAL = 3 };
 
@@ -157,8 +162,4 @@ inline int col_g_threads(const FftPlan& pl) {
 inline size_t col_g_lds_bytes(const shs_plan* p, int extra) {
   return (size_t(extra + col_bufs(p->pcol)) * p->n * kGW + col_tab_len(p->n)) * sizeof(float2);
 }
-// Reserves the dynamic LDS of the generic column passes for the largest supported side;
-// false if the runtime refuses.
-bool mixed_reserve_lds();
-
 }  // namespace shs

@@ -338,6 +338,7 @@ struct RowParams {
   long long real_cs;       // channel stride of real rows (floats)
   int eta;                 // filters per label: filter of channel ch is ch % eta
   int emit;                // SOLVE: write the next adjoint input spectrum
+  int fresh;               // SOLVE, PD: the state is zero and need not be read
   float sigma;             // PD: dual step size
   FilterWeights fw;        // passed by value (kernel argument memory)
 };
@@ -484,8 +485,8 @@ __device__ __forceinline__ void row_body(const RowParams& p, BlockId bid) {
     // one contiguous run per row.  Only this pass reads or writes the state.
     gp = reinterpret_cast<typename S::T*>(p.g) + (long long)ch * N * N + (long long)row * N;
     static_for<G::R / PV::V>([&](auto i) {
-      typename S::Pair v[PV::V];
-      PV::load(gp + 2 * PV::V * (i * G::T + t), v);
+      typename S::Pair v[PV::V] = {};
+      if (!p.fresh) PV::load(gp + 2 * PV::V * (i * G::T + t), v);
       static_for<PV::V>([&](auto e) { gv[i * PV::V + e] = v[e]; });
     });
   }
@@ -861,18 +862,6 @@ __global__ __launch_bounds__(ColCfg<N>::THREADS) __attribute__((amdgpu_waves_per
 }
 
 // ---------------------------------------------------------------- per-pixel u / w step
-struct PixParams {
-  const float* z;      // S^T (v - b_v) per label [q][N^2] (null on the first iteration)
-  float* w;            // w   [q][N^2]  (read, written)
-  float* bw;           // b_w [q][N^2]  (read, written)
-  const float* s;      // data term [q][N^2]
-  float* u;            // u   [q][N^2]  (written)
-  double* partials;    // [blocks][4]
-  long long n2;
-  float gamma;
-  int q;
-};
-
 // Projection of one label vector onto the simplex C, in place: the paper's procedure
 // (project onto the hyperplane sum = 1, drop the entries that are not positive,
 // re-project the rest, until none is dropped; at most q rounds).
@@ -900,105 +889,184 @@ __device__ __forceinline__ void simplex_project(float (&g)[MQ], int q) {
   for (int l = 0; l < MQ; ++l) g[l] = act[l] ? (cnt == 1 ? 1.f : g[l] - tau) : 0.f;
 }
 
-// u = 1/2 [z + (w - b_w) - gamma s]  (Section 3 u-update, A^T A = 2I);
-// g_w = b_w + u;  w = P_C(g_w) (pixelwise simplex);  b_w = g_w - w.
-template <bool STATS, bool HAVE_Z>
-__device__ __forceinline__ void pixel_body(const PixParams& p, BlockId bid) {
-  constexpr int MQ = 8;
-  __shared__ double red[4 * 4];
-  const long long i = (long long)bid.x * 256 + threadIdx.x;
-  const bool active = i < p.n2;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (active) {
-    float gw[MQ], wn[MQ], wo[MQ], bo[MQ], sv[MQ];
-#pragma unroll
-    for (int l = 0; l < MQ; ++l) {
-      gw[l] = 0.f;
-      if (l < p.q) {
-        const long long o = l * p.n2 + i;
-        const float z = HAVE_Z ? p.z[o] : 0.f;
-        wo[l] = p.w[o]; bo[l] = p.bw[o]; sv[l] = p.s[o];
-        const float u = 0.5f * (z + (wo[l] - bo[l]) - p.gamma * sv[l]);
-        p.u[o] = u;
-        gw[l] = bo[l] + u;
+// The step between the adjoint's column passes and the forward transform's, one kernel: the
+// labels' adjoint rows back to pixels (inverse row transform of Z), the pixel step, and the
+// row transform of its result (V).  The pixel step needs all labels of a pixel and the row
+// transforms a whole row of one label, so a block holds RB rows of all q labels in LDS; the
+// images between the three parts are never stored.
+//   ADMM:  u = 1/2 [z + (w - b_w) - gamma s]  (Section 3 u-update, A^T A = 2I);
+//          g_w = b_w + u;  w = P_C(g_w) (pixelwise simplex);  b_w = g_w - w;  V = rowFFT(u)
+//   PD:    u' = P_C(u - tau (z + s)),  V = rowFFT(2 u' - u)   (u in w, tau in gamma)
+enum MidMode { MID_ADMM = 0, MID_PD = 1 };
+struct MidParams {
+  const float2* z;     // S^T (v - b_v) (ADMM) or S^T y (PD): per-label dense spectra, column-transformed
+                       // back; null: first iteration from the zero state, z = w = b_w = 0
+  float2* v;           // row spectra of u or ubar (written when emit)
+  float* w;            // w or the primal u [q][N^2] (read, written)
+  float* bw;           // b_w [q][N^2] (read, written; ADMM)
+  const float* s;      // data term [q][N^2]
+  double* partials;    // [blocks][4]
+  const float2* tw;    // the plan's twiddle table
+  long long n2;
+  int P;               // columns of a dense spectrum plane
+  int q;
+  float gamma;
+  int emit;            // write v
+  int stats;           // write partials
+};
+
+// The pixel step on RB rows from row0, all q labels, spread over the block's nthr threads,
+// two adjacent pixels at a time.  at(l, r, k): the LDS slot of pixels (2k, 2k+1) of row r,
+// label l, which holds z on entry and the next transform's input on return.
+template <int Q, int MODE, bool STATS, class At>
+__device__ __forceinline__ void pixel_rows(const MidParams& p, int row0, int rows, int n, int nthr, double (&acc)[4],
+                                           At&& at) {
+  const int half = n / 2;
+  for (int r = 0; r < rows; ++r)
+  for (int k = threadIdx.x; k < half; k += nthr) {
+    const long long o = (long long)(row0 + r) * n + 2 * k;
+    float2 wo[Q], bo[Q], sv[Q];
+    static_for<Q>([&](auto l) {
+      sv[l] = *reinterpret_cast<const float2*>(p.s + l * p.n2 + o);
+      wo[l] = bo[l] = make_float2(0.f, 0.f);
+      if (p.z) {
+        wo[l] = *reinterpret_cast<const float2*>(p.w + l * p.n2 + o);
+        if constexpr (MODE == MID_ADMM) bo[l] = *reinterpret_cast<const float2*>(p.bw + l * p.n2 + o);
       }
-      wn[l] = gw[l];
-    }
-    simplex_project<MQ>(wn, p.q);
-#pragma unroll
-    for (int l = 0; l < MQ; ++l) {
-      if (l < p.q) {
-        const long long o = l * p.n2 + i;
-        const float bn = gw[l] - wn[l];
-        p.w[o] = wn[l];
-        p.bw[o] = bn;
+    });
+    float gx[Q], gy[Q], wx[Q], wy[Q];
+    static_for<Q>([&](auto l) {
+      cpx z = cpx{0.f, 0.f};
+      if (p.z) z = ld(at(l, r, k));
+      if constexpr (MODE == MID_ADMM) {
+        const float ux = 0.5f * (z.x + (wo[l].x - bo[l].x) - p.gamma * sv[l].x);
+        const float uy = 0.5f * (z.y + (wo[l].y - bo[l].y) - p.gamma * sv[l].y);
+        st(at(l, r, k), cpx{ux, uy});
+        gx[l] = bo[l].x + ux;
+        gy[l] = bo[l].y + uy;
+      } else {
+        gx[l] = wo[l].x - p.gamma * (z.x + sv[l].x);
+        gy[l] = wo[l].y - p.gamma * (z.y + sv[l].y);
+      }
+      wx[l] = gx[l];
+      wy[l] = gy[l];
+    });
+    simplex_project<Q>(wx, Q);
+    simplex_project<Q>(wy, Q);
+    static_for<Q>([&](auto l) {
+      *reinterpret_cast<float2*>(p.w + l * p.n2 + o) = make_float2(wx[l], wy[l]);
+      const float dwx = wx[l] - wo[l].x, dwy = wy[l] - wo[l].y;
+      if constexpr (MODE == MID_ADMM) {
+        const float bx = gx[l] - wx[l], by = gy[l] - wy[l];
+        *reinterpret_cast<float2*>(p.bw + l * p.n2 + o) = make_float2(bx, by);
         if constexpr (STATS) {
-          const float dw = wn[l] - wo[l], db = bn - bo[l];
-          acc[SLOT_DY2] += double(dw) * dw;
-          acc[SLOT_DB2] += double(db) * db;
-          acc[SLOT_WS] += double(wn[l]) * double(sv[l]);
+          const float dbx = bx - bo[l].x, dby = by - bo[l].y;
+          acc[SLOT_DY2] += double(dwx) * dwx + double(dwy) * dwy;
+          acc[SLOT_DB2] += double(dbx) * dbx + double(dby) * dby;
         }
+      } else {
+        st(at(l, r, k), cpx{2.f * wx[l] - wo[l].x, 2.f * wy[l] - wo[l].y});
+        if constexpr (STATS) acc[SLOT_DB2] += double(dwx) * dwx + double(dwy) * dwy;
       }
-    }
+      if constexpr (STATS) acc[SLOT_WS] += double(wx[l]) * double(sv[l].x) + double(wy[l]) * double(sv[l].y);
+    });
   }
-  if constexpr (STATS) {
-    block_sum4<4>(acc, red);
-    if (threadIdx.x == 0) {
-      double* o = p.partials + (long long)bid.x * 4;
-      o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
-    }
+}
+template <int MODE, bool STATS, class At>
+__device__ __forceinline__ void pixel_rows_q(const MidParams& p, int row0, int rows, int n, int nthr, double (&acc)[4],
+                                             At&& at) {
+  switch (p.q) {
+    case 1: pixel_rows<1, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    case 2: pixel_rows<2, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    case 3: pixel_rows<3, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    case 4: pixel_rows<4, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    case 5: pixel_rows<5, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    case 6: pixel_rows<6, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    case 7: pixel_rows<7, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    case 8: pixel_rows<8, MODE, STATS>(p, row0, rows, n, nthr, acc, at); break;
+    default: break;
+  }
+}
+// Writes the block's partial sums.
+__device__ __forceinline__ void mid_partials(const MidParams& p, double (&acc)[4], double* red, int nwaves, BlockId bid) {
+  block_sum4_n(acc, red, nwaves);
+  if (threadIdx.x == 0) {
+    double* o = p.partials + (long long)bid.x * 4;
+    o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
   }
 }
 
-template <bool STATS, bool HAVE_Z>
-__global__ __launch_bounds__(256) void k_pixel(PixParams p) {
-  pixel_body<STATS, HAVE_Z>(p, own_block());
+// Blocks of adjacent rows on one XCD (block b runs on XCD b mod 8): rows share the 128-byte
+// lines of the strips, which that XCD's L2 then serves once.
+__device__ __forceinline__ int xcd_chunked(int b, int blocks) {
+  return blocks % 8 == 0 ? (b & 7) * (blocks / 8) + (b >> 3) : b;
 }
 
-// Primal step of the primal-dual iteration: u_new = P_C(u - tau (K^T y + s)) and the
-// extrapolation ubar = 2 u_new - u.  Here w holds u (read, written), u receives ubar, z
-// holds K^T y, gamma is the primal step tau.  Partials: ||u_new - u||^2, <u_new, s>.
-template <bool STATS>
-__global__ __launch_bounds__(256) void k_pixel_pd(PixParams p) {
-  constexpr int MQ = 8;
-  __shared__ double red[4 * 4];
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  const bool active = i < p.n2;
+// Power-of-two sides: one row per block, so that the launch has blocks for the whole GPU; a
+// wave transforms RPW labels' rows at a time.
+template <int N> struct MidGeom {
+  static constexpr int RB = 1;
+  // waves of a block: enough for the transforms, and for the pixel step as many more (up to one
+  // pixel pair per thread) as keep all rows' blocks on the GPU at once; a power of two (images
+  // of a batch then share a few block sizes).  At N = 1024, q = 5 (four waves, 44 us;
+  // the three separate kernels 58) eight waves took 54: idle during the transforms, they halve
+  // the blocks in flight.
+  static constexpr int waves(int q) {
+    int w = 1;
+    while (w < 8 && (w * RowGeom<N>::RPW < RB * q || (w * 128 < N && w * N < 4096))) w *= 2;
+    return w;
+  }
+  static constexpr size_t lds(int q) { return size_t(RB) * q * RowGeom<N>::LROW * sizeof(float2); }
+};
+template <int N, int MODE, bool STATS>
+__device__ __forceinline__ void mid_body(const MidParams& p, BlockId bid) {
+  using G = RowGeom<N>;
+  constexpr int RB = MidGeom<N>::RB;
+  extern __shared__ float2 gsm[];            // slot (l RB + r): one row's LROW points
+  __shared__ float2 twl[G::TW_LDS];
+  __shared__ double red[8 * 4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int sub = lane / G::T, t = lane % G::T;
+  const int row0 = xcd_chunked(bid.x, bid.gx) * RB, slots = RB * p.q;
+  const long long ls = (long long)N * p.P;
+  for (int e = threadIdx.x; e < G::TW_LDS; e += blockDim.x)
+    twl[e] = p.tw[e < G::TW_PRE ? e : row_sw_off<N>() + (e - G::TW_PRE)];
+  __syncthreads();
+  const int tq = int(unsigned(t) / G::R), tr = int(unsigned(t) % G::R);
+  if (p.z) {
+    for (int s0 = wave * G::RPW; s0 < slots; s0 += nw * G::RPW) {
+      const int s = s0 + sub;
+      if (s < slots) {
+        const RowAddr<G::R> A{gsm + s * G::LROW};
+        cpx a[G::R];
+        row_c2r<N>(a, p.z + (s / RB) * ls, row0 + s % RB, 0, p.P, A, t, twl);
+        fft_sync<SYNC_WAVE>();
+        static_for<G::R>([&](auto r) { st(A.template at<G::R>(tq + r * G::RM, tr), a[r]); });
+      }
+    }
+  }
+  __syncthreads();
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (active) {
-    float un[MQ], uo[MQ], sv[MQ];
-#pragma unroll
-    for (int l = 0; l < MQ; ++l) {
-      un[l] = 0.f;
-      if (l < p.q) {
-        const long long o = l * p.n2 + i;
-        uo[l] = p.w[o];
-        sv[l] = p.s[o];
-        un[l] = uo[l] - p.gamma * (p.z[o] + sv[l]);
-      }
-    }
-    simplex_project<MQ>(un, p.q);
-#pragma unroll
-    for (int l = 0; l < MQ; ++l) {
-      if (l < p.q) {
-        const long long o = l * p.n2 + i;
-        p.w[o] = un[l];
-        p.u[o] = 2.f * un[l] - uo[l];
-        if constexpr (STATS) {
-          const float du = un[l] - uo[l];
-          acc[SLOT_DB2] += double(du) * du;
-          acc[SLOT_WS] += double(un[l]) * double(sv[l]);
-        }
+  pixel_rows_q<MODE, STATS>(p, row0, RB, N, blockDim.x, acc, [&](int l, int r, int k) {
+    return gsm + (l * RB + r) * G::LROW + (k + k / G::R);
+  });
+  __syncthreads();
+  if (p.emit) {
+    for (int s0 = wave * G::RPW; s0 < slots; s0 += nw * G::RPW) {
+      const int s = s0 + sub;
+      if (s < slots) {
+        const RowAddr<G::R> A{gsm + s * G::LROW};
+        cpx a[G::R];
+        static_for<G::R>([&](auto r) { a[r] = ld(A.template at<G::R>(tq + r * G::RM, tr)); });
+        row_r2c<N, false>(a, p.v + (s / RB) * ls, row0 + s % RB, 0, p.P, A, t, twl);
       }
     }
   }
-  if constexpr (STATS) {
-    block_sum4<4>(acc, red);
-    if (threadIdx.x == 0) {
-      double* o = p.partials + (long long)blockIdx.x * 4;
-      o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
-    }
-  }
+  if constexpr (STATS) mid_partials(p, acc, red, nw, bid);
+}
+template <int N, int MODE, bool STATS>
+__global__ __launch_bounds__(64 * MidGeom<N>::waves(8)) void k_mid(MidParams p) {
+  mid_body<N, MODE, STATS>(p, own_block());
 }
 
 }  // namespace shs

@@ -6,7 +6,7 @@
 namespace shs {
 
 inline GenParams mixed_params(const shs_plan* p) {
-  return GenParams{p->prow, p->pfwd, p->pcol, p->n, p->wpb, p->rw == 4 ? 2 : p->rw == 2 ? 1 : 0, p->nbuf};
+  return GenParams{p->fft, p->n, p->wpb, p->rw == 4 ? 2 : p->rw == 2 ? 1 : 0, p->nbuf, 0};
 }
 
 template <int MODE, int ST, bool STATS>

@@ -62,14 +62,21 @@ static void mixed_col_solve(const shs_plan* p, const ColParams& cp, int labels, 
                      mixed_params(p), p->eig);
 }
 
-Ops mixed_ops() { return Ops{&mixed_row_any, &mixed_col_any, &mixed_col_solve}; }
+void mixed_mid(const shs_plan* p, int mode, const MidParams& mp, hipStream_t s);
+int mixed_mid_blocks(const shs_plan* p);
+bool mixed_mid_reserve();
 
-bool mixed_reserve_lds() {
+static bool mixed_reserve() {
   const int bytes = (3 * kGenericMaxN * kGW + col_tab_len(kGenericMaxN)) * int(sizeof(float2));
   return mixed_col_reserve<COL_FWD>() && mixed_col_reserve<COL_SYN>() && mixed_col_reserve<COL_ANA>() &&
          mixed_col_reserve<COL_FINAL>() &&
          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_colg_solve), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             bytes) == hipSuccess;
+                             bytes) == hipSuccess &&
+         mixed_mid_reserve();
+}
+
+Ops mixed_ops() {
+  return Ops{&mixed_row_any, &mixed_col_any, &mixed_col_solve, &mixed_mid, &mixed_mid_blocks, &mixed_reserve};
 }
 
 }  // namespace shs

@@ -72,8 +72,38 @@ void launch_col_solve(const shs_plan* p, const ColParams& cp, int labels, hipStr
 }
 
 template <int N>
+struct MidPipe {
+  template <int MODE, bool STATS>
+  static void launch(const shs_plan* p, const MidParams& mp, hipStream_t s) {
+    const int threads = 64 * MidGeom<N>::waves(p->q);
+    const size_t lds = MidGeom<N>::lds(p->q);
+    if constexpr (MODE == MID_ADMM) {
+      if (g_rec) {
+        rec_add(RK_MID, &kg_mid<N, STATS>, threads, blocks(p), 1, lds).mp = mp;
+        return;
+      }
+    }
+    hipLaunchKernelGGL((k_mid<N, MODE, STATS>), dim3(blocks(p)), dim3(threads), lds, s, mp);
+  }
+  static int blocks(const shs_plan*) { return N / MidGeom<N>::RB; }
+  static void mid(const shs_plan* p, int mode, const MidParams& mp, hipStream_t s) {
+    if (mode == MID_PD) mp.stats ? launch<MID_PD, true>(p, mp, s) : launch<MID_PD, false>(p, mp, s);
+    else mp.stats ? launch<MID_ADMM, true>(p, mp, s) : launch<MID_ADMM, false>(p, mp, s);
+  }
+  static bool reserve() {
+    const auto one = [](auto fn) {
+      return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 int(MidGeom<N>::lds(SHS_MAX_LABELS))) == hipSuccess;
+    };
+    return one(&k_mid<N, MID_ADMM, true>) && one(&k_mid<N, MID_ADMM, false>) && one(&k_mid<N, MID_PD, true>) &&
+           one(&k_mid<N, MID_PD, false>) && one(&kg_mid<N, true>) && one(&kg_mid<N, false>);
+  }
+};
+
+template <int N>
 Ops pow2_ops() {
-  return Ops{&Pipe<N>::row, &Pipe<N>::col, &launch_col_solve<N>};
+  return Ops{&Pipe<N>::row, &Pipe<N>::col, &launch_col_solve<N>, &MidPipe<N>::mid, &MidPipe<N>::blocks,
+             &MidPipe<N>::reserve};
 }
 
 }  // namespace shs

@@ -61,7 +61,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // ---------------------------------------------------------------- kernel timing
 enum KClass {
   KC_ROW_SOLVE, KC_COL_SYN, KC_COL_ANA, KC_COL_FINAL, KC_COL_FWD, KC_ROW_C2R, KC_ROW_R2C, KC_ROW_PRIME,
-  KC_ROW_ENERGY, KC_PIXEL, KC_REDUCE, KC_OTHER, KC_BATCH, KC_ROW_SHRINK, KC_ROW_PD, KC_TV_RHS, KC_TV_UPDATE,
+  KC_ROW_ENERGY, KC_MID, KC_REDUCE, KC_OTHER, KC_BATCH, KC_ROW_SHRINK, KC_ROW_PD, KC_TV_RHS, KC_TV_UPDATE,
   KC_COL_SOLVE, KC_NL_DUAL, KC_NL_PRIMAL, KC_COUNT
 };
 const char* const kKClassName[KC_COUNT] = {"row_solve", "col_syn", "col_ana", "col_final", "col_fwd", "row_c2r",
@@ -419,15 +419,9 @@ void run_col_solve(const Ctx& c, const ColParams& cp, int labels) {
   c.ops.col_solve(c.p, cp, labels, c.s);
 }
 
-// S: real images [count][N][N] -> pruned coefficient spectra T1 (count * eta planes).
-void enqueue_synthesis(const Ctx& c, const float* real_in, int count) {
+// Row spectra V (count dense planes) -> pruned coefficient spectra T1 (count * eta planes).
+void enqueue_synthesis_cols(const Ctx& c, int count) {
   const shs_plan* p = c.p;
-  RowParams rp{};
-  rp.real_in = real_in;
-  rp.spec_out = c.at<float2>(c.L.v);
-  rp.lout = dense_layout(p);
-  rec_step(BS_R2C);
-  run_row(c, ROW_R2C, ST_F32, false, rp, count);
   ColParams cp = col_params(c, count);
   cp.in = c.at<float2>(c.L.v);
   cp.out = c.at<float2>(c.L.v);          // column FFT in place: V -> U
@@ -438,6 +432,38 @@ void enqueue_synthesis(const Ctx& c, const float* real_in, int count) {
   cp.items = p->items_syn;
   rec_step(BS_SYN);
   run_col(c, COL_SYN, cp, p->n_syn, count);
+}
+
+// S: real images [count][N][N] -> pruned coefficient spectra T1.
+void enqueue_synthesis(const Ctx& c, const float* real_in, int count) {
+  RowParams rp{};
+  rp.real_in = real_in;
+  rp.spec_out = c.at<float2>(c.L.v);
+  rp.lout = dense_layout(c.p);
+  run_row(c, ROW_R2C, ST_F32, false, rp, count);
+  enqueue_synthesis_cols(c, count);
+}
+
+// The middle step of a solver iteration (MID_*): Z -> pixels -> V.
+void run_mid(const Ctx& c, int mode, const float* d_s, float gamma, bool have_z, bool stats, bool emit) {
+  const shs_plan* p = c.p;
+  MidParams mp{};
+  mp.z = have_z ? c.at<float2>(c.L.z) : nullptr;
+  mp.v = c.at<float2>(c.L.v);
+  mp.w = c.at<float>(c.L.w);
+  mp.bw = c.at<float>(c.L.bw);
+  mp.s = d_s;
+  mp.partials = c.at<double>(c.L.parts) + c.L.nrow_parts * 4;
+  mp.tw = p->tw;
+  mp.n2 = (long long)p->n * p->n;
+  mp.P = p->P;
+  mp.q = p->q;
+  mp.gamma = gamma;
+  mp.emit = emit ? 1 : 0;
+  mp.stats = stats ? 1 : 0;
+  rec_step(BS_MID);
+  Timed tm(c.s, KC_MID);
+  c.ops.mid(p, mode, mp, c.s);
 }
 
 // Adjoint column side: pruned spectra T2 (count * eta planes) -> Z (count dense planes).
@@ -529,7 +555,7 @@ shs_status energy_of(const Ctx& c, const float* d_u, const float* d_s, double* o
 void free_plan(shs_plan* p) {
   if (!p) return;
   delete p->graphs;
-  void* bufs[] = {p->psi, p->tw, p->eig, p->psiw, p->pwin, p->tcol, p->items_syn, p->items_ana, p->fwin,
+  void* bufs[] = {p->psi, p->tw, p->fft, p->eig, p->psiw, p->pwin, p->tcol, p->items_syn, p->items_ana, p->fwin,
                   p->fgeo, p->strips_ana};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
@@ -662,12 +688,15 @@ shs_status check_params(const shs_params* prm) {
   return SHS_OK;
 }
 
-// Zero ADMM state (v = w = b = 0) with a fill kernel, so that it can be captured in a graph.
-void enqueue_zero_state(const Ctx& c) {
-  const long long words = (long long)(c.L.state_end / 4);
+// Zeroes `bytes` (a multiple of 4) of the workspace from `off` with a fill kernel, so that it
+// can be captured in a graph.
+void enqueue_zero(const Ctx& c, size_t off, size_t bytes) {
+  const long long words = (long long)(bytes / 4);
   hipLaunchKernelGGL(k_fill_u32, dim3(unsigned((words + 255) / 256)), dim3(256), 0, c.s,
-                     reinterpret_cast<uint32_t*>(c.ws + c.L.g), words, 0u);
+                     reinterpret_cast<uint32_t*>(c.ws + off), words, 0u);
 }
+// Zero solver state (v = w = b = 0).
+void enqueue_zero_state(const Ctx& c) { enqueue_zero(c, c.L.g, c.L.state_end - c.L.g); }
 
 void enqueue_epilogue(const Ctx& c, float* d_u, int32_t* d_labels) {
   if (!d_u && !d_labels) return;
@@ -686,44 +715,9 @@ void enqueue_iteration(const Ctx& c, const float* d_s, float gamma, bool have_ad
   const shs_plan* p = c.p;
   const Layout& L = c.L;
   const int q = p->q;
-  const long long n2 = (long long)p->n * p->n;
-  const long long npix_blocks = (n2 + 255) / 256;
-  if (have_adjoint_input) {
-    enqueue_analysis(c, q);
-    RowParams rz{};
-    rz.spec_in = c.at<float2>(L.z);
-    rz.lin = dense_layout(p);
-    rz.real_out = c.at<float>(L.zs);
-    rec_step(BS_C2R);
-    run_row(c, ROW_C2R, ST_F32, false, rz, q);
-  }
-  PixParams pp{};
-  pp.z = c.at<float>(L.zs);
-  pp.w = c.at<float>(L.w);
-  pp.bw = c.at<float>(L.bw);
-  pp.s = d_s;
-  pp.u = c.at<float>(L.us);
-  pp.partials = c.at<double>(L.parts) + L.nrow_parts * 4;
-  pp.n2 = n2;
-  pp.gamma = gamma;
-  pp.q = q;
-  rec_step(BS_PIXEL);
-  if (g_rec) {
-    auto fn = have_adjoint_input ? (stats ? &kg_pixel<true, true> : &kg_pixel<false, true>)
-                                 : (stats ? &kg_pixel<true, false> : &kg_pixel<false, false>);
-    rec_add(RK_PIX, fn, 256, int(npix_blocks), 1, 0).pp = pp;
-  } else {
-    Timed tm(c.s, KC_PIXEL);
-    const dim3 g{unsigned(npix_blocks)}, b{256};
-    if (have_adjoint_input) {
-      if (stats) hipLaunchKernelGGL((k_pixel<true, true>), g, b, 0, c.s, pp);
-      else hipLaunchKernelGGL((k_pixel<false, true>), g, b, 0, c.s, pp);
-    } else {
-      if (stats) hipLaunchKernelGGL((k_pixel<true, false>), g, b, 0, c.s, pp);
-      else hipLaunchKernelGGL((k_pixel<false, false>), g, b, 0, c.s, pp);
-    }
-  }
-  enqueue_synthesis(c, c.at<float>(L.us), q);
+  if (have_adjoint_input) enqueue_analysis(c, q);
+  run_mid(c, MID_ADMM, d_s, gamma, have_adjoint_input, stats, true);
+  enqueue_synthesis_cols(c, q);
   RowParams rp{};
   rp.spec_in = c.at<float2>(L.t1);
   rp.lin = pruned_layout(p);
@@ -731,9 +725,10 @@ void enqueue_iteration(const Ctx& c, const float* d_s, float gamma, bool have_ad
   rp.lout = pruned_layout(p);
   rp.g = c.ws + L.g;
   rp.emit = emit ? 1 : 0;
+  rp.fresh = have_adjoint_input ? 0 : 1;
   rec_step(BS_ROW);
   run_row(c, ROW_SOLVE, p->store, stats, rp, q * p->eta);
-  if (stats) enqueue_reduce(c, L.nrow_parts + npix_blocks, hist_row, gamma, hist_ctr);
+  if (stats) enqueue_reduce(c, L.nrow_parts + c.ops.mid_blocks(p), hist_row, gamma, hist_ctr);
 }
 
 template <int ST>
@@ -822,16 +817,16 @@ shs_status tv_energy_of(const Ctx& c, const float* d_s, float lambda, double* ou
   return SHS_OK;
 }
 
-// One primal-dual iteration (Chambolle-Pock for the functional of Section 3):
-// K ubar (synthesis), the dual step fused into the row pass (y <- clip(y + sigma K ubar),
-// then the row FFT of y), K^T y (analysis), the primal step and extrapolation per pixel.
-void enqueue_pd_iteration(const Ctx& c, const float* d_s, float tau, float sigma, bool stats, double* hist_row) {
+// One primal-dual iteration (Chambolle-Pock for the functional of Section 3), from the row
+// spectra of ubar: K ubar (synthesis), the dual step fused into the row pass (y <- clip(y +
+// sigma K ubar), then the row FFT of y), K^T y (analysis), the primal step and extrapolation
+// with their row transforms (the next ubar's spectra unless this is the last iteration).
+void enqueue_pd_iteration(const Ctx& c, const float* d_s, float tau, float sigma, bool first, bool last, bool stats,
+                          double* hist_row) {
   const shs_plan* p = c.p;
   const Layout& L = c.L;
   const int q = p->q;
-  const long long n2 = (long long)p->n * p->n;
-  const long long npix_blocks = (n2 + 255) / 256;
-  enqueue_synthesis(c, c.at<float>(L.us), q);
+  enqueue_synthesis_cols(c, q);
   RowParams rp{};
   rp.spec_in = c.at<float2>(L.t1);
   rp.lin = pruned_layout(p);
@@ -839,30 +834,12 @@ void enqueue_pd_iteration(const Ctx& c, const float* d_s, float tau, float sigma
   rp.lout = pruned_layout(p);
   rp.g = c.ws + L.g;
   rp.emit = 1;
+  rp.fresh = first ? 1 : 0;
   rp.sigma = sigma;
   run_row(c, ROW_PD, p->store, stats, rp, q * p->eta);
   enqueue_analysis(c, q);
-  RowParams rz{};
-  rz.spec_in = c.at<float2>(L.z);
-  rz.lin = dense_layout(p);
-  rz.real_out = c.at<float>(L.zs);
-  run_row(c, ROW_C2R, ST_F32, false, rz, q);
-  PixParams pp{};
-  pp.z = c.at<float>(L.zs);
-  pp.w = c.at<float>(L.w);
-  pp.s = d_s;
-  pp.u = c.at<float>(L.us);
-  pp.partials = c.at<double>(L.parts) + L.nrow_parts * 4;
-  pp.n2 = n2;
-  pp.gamma = tau;
-  pp.q = q;
-  {
-    Timed tm(c.s, KC_PIXEL);
-    const dim3 g{unsigned(npix_blocks)}, b{256};
-    if (stats) hipLaunchKernelGGL((k_pixel_pd<true>), g, b, 0, c.s, pp);
-    else hipLaunchKernelGGL((k_pixel_pd<false>), g, b, 0, c.s, pp);
-  }
-  if (stats) enqueue_reduce(c, L.nrow_parts + npix_blocks, hist_row, 1.0);
+  run_mid(c, MID_PD, d_s, tau, true, stats, !last);
+  if (stats) enqueue_reduce(c, L.nrow_parts + c.ops.mid_blocks(p), hist_row, 1.0);
 }
 
 // KIND 0: dual step, 1: primal step of the NL primal-dual iteration.
@@ -985,7 +962,7 @@ void build_batch_iter(const std::vector<LaunchRec>& recs, std::vector<char>& are
       const int kind = groups[g][0]->kind;
       if (kind == RK_ROW) put_group(groups[g], &LaunchRec::rp, arena, it);
       else if (kind == RK_COL) put_group(groups[g], &LaunchRec::cp, arena, it);
-      else put_group(groups[g], &LaunchRec::pp, arena, it);
+      else put_group(groups[g], &LaunchRec::mp, arena, it);
       out.push_back(it);
     }
   }
@@ -1094,7 +1071,9 @@ shs_status apply_schedule(shs_plan* p, const TuneCfg& c, const StripLists& sl) {
   const std::vector<float2> tw = base_twiddles(n);
   std::vector<float2> tabs(size_t(n) / 2 * 3 + n);
   fill_stage_tables_g(pr, pf, pc, tw, tabs.data());
+  const FftPlan plans[3] = {pr, pf, pc};
   HIPCHK(hipMemcpy(p->tw + n, tabs.data(), tabs.size() * sizeof(float2), hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(p->fft, plans, sizeof(plans), hipMemcpyHostToDevice));
   p->prow = pr;
   p->pfwd = pf;
   p->pcol = pc;
@@ -1500,6 +1479,14 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
     const double sn = std::sin(M_PI * double(k) / double(n));
     eig[k] = float(4.0 * sn * sn);
   }
+  if (!pow2) {
+    const FftPlan plans[3] = {p->prow, p->pfwd, p->pcol};
+    if (hipMalloc(&p->fft, sizeof(plans)) != hipSuccess) { free_plan(p); return fail(SHS_E_NOMEM, "stage lists"); }
+    if (hipMemcpy(p->fft, plans, sizeof(plans), hipMemcpyHostToDevice) != hipSuccess) {
+      free_plan(p);
+      return fail(SHS_E_DEVICE, "stage list copy");
+    }
+  }
   if (hipMalloc(&p->eig, size_t(n) * 4) != hipSuccess) { free_plan(p); return fail(SHS_E_NOMEM, "eigenvalue table"); }
   if (hipMemcpy(p->eig, eig.data(), size_t(n) * 4, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(p->tw, tw.data(), tw.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
@@ -1514,12 +1501,14 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
     free_plan(p);
     return fail(SHS_E_DEVICE, "filter generation failed");
   }
-  // generic column passes hold their twiddle table and 3 strips of N x 4 bins in dynamic LDS
-  // (up to 104 KB); the cap is set for the largest supported N, so plans of any size can be
-  // created in any order
-  if (p->generic && !mixed_reserve_lds()) {
-    free_plan(p);
-    return fail(SHS_E_DEVICE, "cannot reserve LDS for the mixed-radix column passes");
+  // kernels whose dynamic LDS exceeds the default limit; the cap is set for the largest plan of
+  // the path, so plans can be created in any order
+  {
+    Ops ops;
+    if (!get_ops(p, ops) || !ops.reserve()) {
+      free_plan(p);
+      return fail(SHS_E_DEVICE, "cannot reserve LDS for the plan's kernels");
+    }
   }
   StripLists sl;
   shs_status st = build_pruned_layout(p, &sl);
@@ -1589,20 +1578,17 @@ shs_status shs_solve_pd(const shs_plan* p, const shs_pd_params* prm, const float
   lp.gamma = 1.f;                        // thresholds = lambda_j (the dual box)
   if ((st = set_lambda(c, &lp)) != SHS_OK) return st;
   const long long n2 = (long long)p->n * p->n;
-  // zero start: y (in the g array), u (in w) and ubar
-  enqueue_zero_state(c);
-  {
-    const long long words = (long long)p->q * n2;
-    hipLaunchKernelGGL(k_fill_u32, dim3(unsigned((words + 255) / 256)), dim3(256), 0, c.s,
-                       reinterpret_cast<uint32_t*>(c.at<float>(c.L.us)), words, 0u);
-  }
+  // zero start: u (in w) and the spectra of ubar; y (in the g array) is written, not read, by
+  // the first iteration
+  enqueue_zero(c, c.L.w, size_t(p->q) * n2 * 4);
+  enqueue_zero(c, c.L.v, size_t(p->q) * p->n * p->P * 8);
   LAUNCHCHK("initial state");
   double tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   bool have = false;
   for (int it = 0; it < prm->iters; ++it) {
     const bool last = it == prm->iters - 1;
     const bool stats = d_hist != nullptr || (last && h_stats != nullptr);
-    enqueue_pd_iteration(c, d_s, prm->tau, prm->sigma, stats, d_hist ? d_hist + 4LL * it : nullptr);
+    enqueue_pd_iteration(c, d_s, prm->tau, prm->sigma, it == 0, last, stats, d_hist ? d_hist + 4LL * it : nullptr);
     LAUNCHCHK("primal-dual iteration");
     if (last && h_stats) {
       HIPCHK(hipMemcpyAsync(tot, c.at<double>(c.L.sdev), 5 * 8, hipMemcpyDeviceToHost, c.s));
@@ -1925,7 +1911,8 @@ shs_status solve_impl(const shs_plan* p, const shs_params* prm, const float* d_s
   const int q = p->q;
   const long long n2 = (long long)p->n * p->n;
   if (!prm->resume) {
-    enqueue_zero_state(c);
+    // the first iteration writes the whole state without reading it
+    if (prm->iters == 0) enqueue_zero_state(c);
   } else {
     RowParams rp{};
     rp.g = c.ws + c.L.g;
@@ -2180,7 +2167,7 @@ shs_status shs_solve_batch(shs_batch* b, const shs_params* params, const float* 
         ok = hipStreamWaitEvent(ls, b->fork, 0) == hipSuccess;
         for (int i : b->lanes[l]) {
           ctx[i].s = ls;
-          enqueue_zero_state(ctx[i]);
+          if (iters == 0) enqueue_zero_state(ctx[i]);
         }
         if (iters >= 1) launch_batch_iter(its[l][0], dbase, ls);
         for (int it = 1; it + 1 < iters; ++it) launch_batch_iter(its[l][1], dbase, ls);
