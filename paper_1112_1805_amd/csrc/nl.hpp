@@ -1,6 +1,5 @@
 // Nonlocal regulariser of Section 4: the NL-means neighbour graph (host, built once per
-// image) and the primal-dual iteration for  <u, s> + lambda sum_i ||(D u)(i)|| + iota_C(u)
-// with D the graph's difference operator (device kernels).
+// image); the iteration on it is in nl_iter.hpp.
 //
 // Graph: for every pixel i in row-major order, with l its number of weights already set,
 // pick k = min(m, 2m - l) eligible pixels j of smallest Gaussian-weighted patch distance
@@ -15,7 +14,8 @@
 #include <thread>
 #include <vector>
 
-#include "kernels.hpp"
+#include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace shs {
 
@@ -182,167 +182,6 @@ inline int nl_build_graph(const NlGraphCfg& g, const float* img, int32_t* nbr, i
     }
   }
   return maxdeg;
-}
-
-// ---------------------------------------------------------------- device iteration
-constexpr int kNlMaxBlocks = 16;
-
-struct NlParams {
-  void* y;              // dual variable [q][M2][n^2] (storage type)
-  float* u;             // primal u [q][n^2] (read, written)
-  float* ubar;          // extrapolation [q][n^2] (read by the dual step, written by the primal step)
-  const float* s;       // data term [q][n^2]
-  const int32_t* nbr;   // [M2][n^2]
-  const int32_t* rev;   // [M2][n^2]
-  double* partials;     // [blocks][4]
-  long long n2;
-  int q, M2;
-  float lambda, tau, sigma;
-};
-
-// y <- P_ball(y + sigma D ubar) per pixel over (label, block), radius lambda.  Partials:
-// ||y' - y||^2 and lambda ||(D ubar)(i)||.  Two passes over the pixel's entries (norm,
-// then scaled store) keep the register footprint independent of q * M2.
-template <int ST, bool STATS>
-__global__ __launch_bounds__(256) void k_nl_dual(NlParams p) {
-  using S = Store<ST>;
-  __shared__ double red[4 * 4];
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (i < p.n2) {
-    typename S::T* y = reinterpret_cast<typename S::T*>(p.y);
-    int nj[kNlMaxBlocks];
-#pragma unroll
-    for (int b = 0; b < kNlMaxBlocks; ++b) nj[b] = b < p.M2 ? p.nbr[b * p.n2 + i] : -1;
-    float nn = 0.f, kk = 0.f;
-    for (int l = 0; l < p.q; ++l) {
-      const float* ub = p.ubar + l * p.n2;
-      const float ui = ub[i];
-#pragma unroll
-      for (int b = 0; b < kNlMaxBlocks; ++b) {
-        if (b < p.M2) {
-          const float z = nj[b] >= 0 ? ub[nj[b]] - ui : 0.f;
-          const float v = fmaf(p.sigma, z, S::to_float(y[(l * p.M2 + b) * p.n2 + i]));
-          nn = fmaf(v, v, nn);
-          kk = fmaf(z, z, kk);
-        }
-      }
-    }
-    const float sc = nn > p.lambda * p.lambda ? p.lambda * rsqrtf(nn) : 1.f;
-    float d2 = 0.f;
-    for (int l = 0; l < p.q; ++l) {
-      const float* ub = p.ubar + l * p.n2;
-      const float ui = ub[i];
-#pragma unroll
-      for (int b = 0; b < kNlMaxBlocks; ++b) {
-        if (b < p.M2) {
-          const long long o = (l * p.M2 + b) * p.n2 + i;
-          const float z = nj[b] >= 0 ? ub[nj[b]] - ui : 0.f;
-          const float yo = S::to_float(y[o]);
-          const float yn = S::round(fmaf(p.sigma, z, yo) * sc);
-          y[o] = S::from_float(yn);
-          d2 = fmaf(yn - yo, yn - yo, d2);
-        }
-      }
-    }
-    if constexpr (STATS) {
-      acc[SLOT_DY2] = d2;
-      acc[SLOT_L1] = double(p.lambda) * sqrt(double(kk));
-    }
-  }
-  if constexpr (STATS) {
-    block_sum4<4>(acc, red);
-    if (threadIdx.x == 0) {
-      double* o = p.partials + (long long)blockIdx.x * 4;
-      o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
-    }
-  }
-}
-
-// u' = P_C(u - tau (D^T y + s)), ubar = 2 u' - u, with
-// (D^T y)(j) = sum_c [j has a c-th neighbour i] (y_{rev_c(j)}(i) - y_c(j)).
-template <int ST, bool STATS>
-__global__ __launch_bounds__(256) void k_nl_primal(NlParams p) {
-  using S = Store<ST>;
-  constexpr int MQ = 8;
-  __shared__ double red[4 * 4];
-  const long long j = (long long)blockIdx.x * 256 + threadIdx.x;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (j < p.n2) {
-    const typename S::T* y = reinterpret_cast<const typename S::T*>(p.y);
-    int ni[kNlMaxBlocks], rb[kNlMaxBlocks];
-#pragma unroll
-    for (int c = 0; c < kNlMaxBlocks; ++c) {
-      ni[c] = c < p.M2 ? p.nbr[c * p.n2 + j] : -1;
-      rb[c] = c < p.M2 ? p.rev[c * p.n2 + j] : 0;
-    }
-    float un[MQ], uo[MQ], sv[MQ];
-#pragma unroll
-    for (int l = 0; l < MQ; ++l) {
-      un[l] = 0.f;
-      if (l < p.q) {
-        float kt = 0.f;
-#pragma unroll
-        for (int c = 0; c < kNlMaxBlocks; ++c) {
-          if (ni[c] >= 0) {
-            kt += S::to_float(y[(l * p.M2 + rb[c]) * p.n2 + ni[c]]) - S::to_float(y[(l * p.M2 + c) * p.n2 + j]);
-          }
-        }
-        uo[l] = p.u[l * p.n2 + j];
-        sv[l] = p.s[l * p.n2 + j];
-        un[l] = uo[l] - p.tau * (kt + sv[l]);
-      }
-    }
-    simplex_project<MQ>(un, p.q);
-#pragma unroll
-    for (int l = 0; l < MQ; ++l) {
-      if (l < p.q) {
-        const long long o = l * p.n2 + j;
-        p.u[o] = un[l];
-        p.ubar[o] = 2.f * un[l] - uo[l];
-        if constexpr (STATS) {
-          const float du = un[l] - uo[l];
-          acc[SLOT_DB2] += double(du) * du;
-          acc[SLOT_WS] += double(un[l]) * double(sv[l]);
-        }
-      }
-    }
-  }
-  if constexpr (STATS) {
-    block_sum4<4>(acc, red);
-    if (threadIdx.x == 0) {
-      double* o = p.partials + (long long)blockIdx.x * 4;
-      o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
-    }
-  }
-}
-
-// Energy partials of u: <u, s> and lambda sum_i (sum_{l, b} (D_b u_l)(i)^2)^(1/2), FP64.
-static __global__ __launch_bounds__(256) void k_nl_energy(NlParams p) {
-  __shared__ double red[4 * 4];
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (i < p.n2) {
-    double nn = 0.0;
-    for (int l = 0; l < p.q; ++l) {
-      const float* u = p.u + l * p.n2;
-      const double ui = u[i];
-      acc[SLOT_WS] += ui * double(p.s[l * p.n2 + i]);
-      for (int b = 0; b < p.M2; ++b) {
-        const int jb = p.nbr[b * p.n2 + i];
-        if (jb >= 0) {
-          const double d = double(u[jb]) - ui;
-          nn += d * d;
-        }
-      }
-    }
-    acc[SLOT_L1] = double(p.lambda) * sqrt(nn);
-  }
-  block_sum4<4>(acc, red);
-  if (threadIdx.x == 0) {
-    double* o = p.partials + (long long)blockIdx.x * 4;
-    o[0] = acc[0]; o[1] = acc[1]; o[2] = acc[2]; o[3] = acc[3];
-  }
 }
 
 }  // namespace shs

@@ -18,6 +18,7 @@
 #include "misc.hpp"
 #include "tv.hpp"
 #include "nl.hpp"
+#include "nl_launch.hpp"
 
 thread_local shs::Recorder* shs::g_rec = nullptr;
 
@@ -840,19 +841,6 @@ void enqueue_pd_iteration(const Ctx& c, const float* d_s, float tau, float sigma
   enqueue_analysis(c, q);
   run_mid(c, MID_PD, d_s, tau, true, stats, !last);
   if (stats) enqueue_reduce(c, L.nrow_parts + c.ops.mid_blocks(p), hist_row, 1.0);
-}
-
-// KIND 0: dual step, 1: primal step of the NL primal-dual iteration.
-template <int ST, int KIND>
-void launch_nl(bool stats, long long npix, hipStream_t s, const NlParams& p) {
-  const dim3 g{unsigned(npix)}, b{256};
-  if constexpr (KIND == 0) {
-    if (stats) hipLaunchKernelGGL((k_nl_dual<ST, true>), g, b, 0, s, p);
-    else hipLaunchKernelGGL((k_nl_dual<ST, false>), g, b, 0, s, p);
-  } else {
-    if (stats) hipLaunchKernelGGL((k_nl_primal<ST, true>), g, b, 0, s, p);
-    else hipLaunchKernelGGL((k_nl_primal<ST, false>), g, b, 0, s, p);
-  }
 }
 
 }  // namespace
@@ -1706,26 +1694,34 @@ shs_status shs_solve_nl(const shs_plan* p, const shs_nl_params* prm, const float
   if (st != SHS_OK) return st;
   const long long n2 = (long long)p->n * p->n;
   const long long npix = (n2 + 255) / 256;
-  enqueue_zero_state(c);
-  {
-    const long long words = (long long)p->q * n2;
-    hipLaunchKernelGGL(k_fill_u32, dim3(unsigned((words + 255) / 256)), dim3(256), 0, c.s,
-                       reinterpret_cast<uint32_t*>(c.at<float>(c.L.us)), words, 0u);
-  }
-  LAUNCHCHK("initial state");
+  // Zero start: u; y and ubar are written, not read, by the first iteration.  The records of y
+  // (16-bit types: padded to whole words) take the state's place, or where they do not fit
+  // there the spectra's, which this solver does not use; the neighbour records' indexes follow.
+  enqueue_zero(c, c.L.w, size_t(p->q) * n2 * 4);
+  const size_t ybytes = align256(size_t(prm->blocks) * n2 * nl_record_bytes(p->store, p->q));
+  const size_t ibytes = align256(size_t(prm->blocks) * n2 * 4);
+  const bool in_state = ybytes <= c.L.w - c.L.g, idx_in_state = in_state && ybytes + ibytes <= c.L.w - c.L.g;
+  const size_t yoff = in_state ? c.L.g : c.L.t1;
+  const size_t ioff = idx_in_state ? c.L.g + ybytes : in_state ? c.L.t1 : c.L.t1 + ybytes;
+  if ((in_state ? (idx_in_state ? 0 : ibytes) : ybytes + ibytes) > c.L.zs - c.L.t1)
+    return fail(SHS_E_UNSUPPORTED, "the graph's blocks do not fit the plan's workspace");
   NlParams np{};
-  np.y = c.ws + c.L.g;
+  np.y = c.ws + yoff;
   np.u = c.at<float>(c.L.w);
   np.ubar = c.at<float>(c.L.us);
+  np.ysum = c.at<float>(c.L.zs);
   np.s = d_s;
   np.nbr = d_nbr;
   np.rev = d_rev;
+  np.src = c.at<int32_t>(ioff);
   np.n2 = n2;
   np.q = p->q;
   np.M2 = prm->blocks;
   np.lambda = prm->lambda;
   np.tau = prm->tau;
   np.sigma = prm->sigma;
+  if (prm->iters > 0) nl_launch(p->store, NL_INDEX, np, c.s);
+  LAUNCHCHK("initial state");
   double tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   bool have = false;
   for (int it = 0; it < prm->iters; ++it) {
@@ -1734,21 +1730,15 @@ shs_status shs_solve_nl(const shs_plan* p, const shs_nl_params* prm, const float
     NlParams pd = np, pp = np;
     pd.partials = c.at<double>(c.L.parts);
     pp.partials = c.at<double>(c.L.parts) + npix * 4;
+    pd.stats = pp.stats = stats ? 1 : 0;
+    pd.fresh = it == 0 ? 1 : 0;
     {
       Timed tm(c.s, KC_NL_DUAL);
-      switch (p->store) {
-        case ST_F32: launch_nl<ST_F32, 0>(stats, npix, c.s, pd); break;
-        case ST_BF16: launch_nl<ST_BF16, 0>(stats, npix, c.s, pd); break;
-        default: launch_nl<ST_F16, 0>(stats, npix, c.s, pd); break;
-      }
+      nl_launch(p->store, NL_DUAL, pd, c.s);
     }
     {
       Timed tm(c.s, KC_NL_PRIMAL);
-      switch (p->store) {
-        case ST_F32: launch_nl<ST_F32, 1>(stats, npix, c.s, pp); break;
-        case ST_BF16: launch_nl<ST_BF16, 1>(stats, npix, c.s, pp); break;
-        default: launch_nl<ST_F16, 1>(stats, npix, c.s, pp); break;
-      }
+      nl_launch(p->store, NL_PRIMAL, pp, c.s);
     }
     if (stats) enqueue_reduce(c, 2 * npix, d_hist ? d_hist + 4LL * it : nullptr, 1.0);
     LAUNCHCHK("NL primal-dual iteration");
@@ -1774,7 +1764,7 @@ shs_status shs_solve_nl(const shs_plan* p, const shs_nl_params* prm, const float
     pe.partials = c.at<double>(c.L.parts);
     {
       Timed tm(c.s, KC_OTHER);
-      hipLaunchKernelGGL(k_nl_energy, dim3(unsigned(npix)), dim3(256), 0, c.s, pe);
+      nl_launch(p->store, NL_ENERGY, pe, c.s);
     }
     enqueue_reduce(c, npix, nullptr, 1.0);
     LAUNCHCHK("NL energy");
