@@ -16,7 +16,7 @@
 
 #include "host.hpp"
 #include "misc.hpp"
-#include "tv.hpp"
+#include "tv_launch.hpp"
 #include "nl.hpp"
 #include "nl_launch.hpp"
 
@@ -732,17 +732,12 @@ void enqueue_iteration(const Ctx& c, const float* d_s, float gamma, bool have_ad
   if (stats) enqueue_reduce(c, L.nrow_parts + c.ops.mid_blocks(p), hist_row, gamma, hist_ctr);
 }
 
-template <int ST>
-void launch_tv_update(bool stats, dim3 grid, hipStream_t s, const TvParams& tp) {
-  if (stats) hipLaunchKernelGGL((k_tv_update<ST, true>), grid, dim3(256), 0, s, tp);
-  else hipLaunchKernelGGL((k_tv_update<ST, false>), grid, dim3(256), 0, s, tp);
-}
-
 TvParams tv_params(const Ctx& c, const float* d_s, float lambda, float gamma) {
   const shs_plan* p = c.p;
   TvParams tp{};
   tp.g = c.ws + c.L.g;
-  tp.g_out = c.ws + c.L.g;
+  tp.t = c.at<float>(c.L.t1);            // the filtered spectra's place, unused here
+  tp.b = c.at<float>(c.L.t2);
   tp.w = c.at<float>(c.L.w);
   tp.bw = c.at<float>(c.L.bw);
   tp.s = d_s;
@@ -760,20 +755,18 @@ TvParams tv_params(const Ctx& c, const float* d_s, float lambda, float gamma) {
 // One ADMM iteration of the TV model: right-hand side (grad^T of v - b_v, w - b_w, data
 // term), the u-solve on the DFT (row R2C, column FFT / divide / inverse, row C2R), then
 // the pixel update of g, w, b_w with residual partials.
-void enqueue_tv_iteration(const Ctx& c, const float* d_s, float lambda, float gamma, bool stats, double* hist_row) {
+void enqueue_tv_iteration(const Ctx& c, const float* d_s, float lambda, float gamma, bool first, bool write_w,
+                          bool stats, double* hist_row) {
   const shs_plan* p = c.p;
   const Layout& L = c.L;
   const int q = p->q;
   const long long n2 = (long long)p->n * p->n;
-  const dim3 gpix{unsigned((n2 + 255) / 256)}, bpix{256};
-  const TvParams tp = tv_params(c, d_s, lambda, gamma);
+  TvParams tp = tv_params(c, d_s, lambda, gamma);
+  tp.fresh = first ? 1 : 0;
+  tp.write_w = write_w ? 1 : 0;
   {
     Timed tm(c.s, KC_TV_RHS);
-    switch (p->store) {
-      case ST_F32: hipLaunchKernelGGL((k_tv_rhs<ST_F32>), gpix, bpix, 0, c.s, tp); break;
-      case ST_BF16: hipLaunchKernelGGL((k_tv_rhs<ST_BF16>), gpix, bpix, 0, c.s, tp); break;
-      default: hipLaunchKernelGGL((k_tv_rhs<ST_F16>), gpix, bpix, 0, c.s, tp); break;
-    }
+    tv_launch(p->store, TV_RHS, false, tp, c.s);
   }
   RowParams rp{};
   rp.real_in = c.at<float>(L.us);
@@ -791,13 +784,9 @@ void enqueue_tv_iteration(const Ctx& c, const float* d_s, float lambda, float ga
   run_row(c, ROW_C2R, ST_F32, false, rz, q);
   {
     Timed tm(c.s, KC_TV_UPDATE);
-    switch (p->store) {
-      case ST_F32: launch_tv_update<ST_F32>(stats, gpix, c.s, tp); break;
-      case ST_BF16: launch_tv_update<ST_BF16>(stats, gpix, c.s, tp); break;
-      default: launch_tv_update<ST_F16>(stats, gpix, c.s, tp); break;
-    }
+    tv_launch(p->store, TV_UPDATE, stats, tp, c.s);
   }
-  if (stats) enqueue_reduce(c, (n2 + 255) / 256, hist_row, gamma);
+  if (stats) enqueue_reduce(c, tv_blocks(n2), hist_row, gamma);
 }
 
 // <w, s> + lambda TV(w) (FP64), synchronising.
@@ -1620,7 +1609,8 @@ shs_status shs_solve_tv(const shs_plan* p, const shs_params* prm, const float* d
   st = make_ctx(p, d_ws, ws_bytes, stream, c);
   if (st != SHS_OK) return st;
   const long long n2 = (long long)p->n * p->n;
-  enqueue_zero_state(c);
+  // the first iteration reads no state
+  if (prm->iters == 0) enqueue_zero_state(c);
   LAUNCHCHK("initial state");
   const double rnorm = std::sqrt(double(p->q) * double(n2));
   double tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -1630,7 +1620,12 @@ shs_status shs_solve_tv(const shs_plan* p, const shs_params* prm, const float* d
     const bool last = it == prm->iters - 1;
     const bool check = prm->tol > 0.0 && ((it + 1) % prm->check_every == 0 || last);
     const bool stats = d_hist != nullptr || check || (last && h_stats != nullptr);
-    enqueue_tv_iteration(c, d_s, lam, prm->gamma, stats, d_hist ? d_hist + 4LL * it : nullptr);
+    // w is read by statistics and by the result only: written where the next iteration or the
+    // end of the solve needs it
+    const bool next_stats = d_hist != nullptr || (it + 2 == prm->iters && h_stats != nullptr) ||
+                            (prm->tol > 0.0 && ((it + 2) % prm->check_every == 0 || it + 2 == prm->iters));
+    enqueue_tv_iteration(c, d_s, lam, prm->gamma, it == 0, last || check || next_stats, stats,
+                         d_hist ? d_hist + 4LL * it : nullptr);
     LAUNCHCHK("TV iteration");
     done = it + 1;
     if (check || (last && h_stats)) {
