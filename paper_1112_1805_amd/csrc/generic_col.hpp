@@ -149,17 +149,26 @@ __device__ __forceinline__ void colg_ana_body(const ColParams& p, const GenParam
     col_transform_g<false>(gp, lsw, b0, b0 + E,
       [&](auto R, int bf, int nb, int c) {
         if constexpr (R <= 16) return psi_load_g<R>(pb, stg.win[i][c], bf, nb, n);
-        else return 0;      // large butterflies: after the transform (registers)
+        else return 0;      // large butterflies: after the transform, in groups (registers)
       },
       StripRead{PlaneBuf(in, E), cols >= kGW, cols},
       [&](auto& a, int bf, int nb, int c, const auto& f0) {
         constexpr int R = sizeof(a) / sizeof(cpx);
-        const auto f = early_or<R <= 16>(f0, [&] { return psi_load_g<R>(pb, stg.win[i][c], bf, nb, n); });
-        static_for<R>([&](auto k) {
+        const auto add = [&](int k, cpx x, float f) {
           float2* o = ba + (bf + k * nb) * kGW + c;
           const cpx old = i == 0 ? cpx{0.f, 0.f} : ld(o);
-          st(o, cpx{fmaf(a[k].x, f.v[k], old.x), fmaf(a[k].y, f.v[k], old.y)});
-        });
+          st(o, cpx{fmaf(x.x, f, old.x), fmaf(x.y, f, old.y)});
+        };
+        if constexpr (R <= 16) {
+          static_for<R>([&](auto k) { add(k, a[k], f0.v[k]); });
+        } else {
+          constexpr int H = 8;
+          static_for<(R + H - 1) / H>([&](auto h) {
+            constexpr int k0 = h * H, cnt = R - k0 < H ? R - k0 : H;
+            const auto f = psi_load_g<cnt>(pb, stg.win[i][c], bf + k0 * nb, nb, n);
+            static_for<cnt>([&](auto m) { add(k0 + m, a[k0 + m], f.v[m]); });
+          });
+        }
       });
     __syncthreads();
   }

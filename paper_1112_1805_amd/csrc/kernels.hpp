@@ -630,6 +630,7 @@ struct ColParams {
   int P, eta, labels;
   int nnz;                // stored filter values in psiw (< 2^29)
   float inv_n2;           // 1 / N^2 (normalisation of the inverse 2-D DFT)
+  int fwd;                // synthesis: `in` holds row spectra V; transform the strip's columns first
 };
 
 constexpr int kItemMax = 16;   // filters per column work item
@@ -713,6 +714,9 @@ __device__ __forceinline__ void col_syn_body(const ColParams& p, BlockId bid) {
   const float2* U = p.in + l * (long long)N * p.P + (long long)it.x * (N * W) + c;
   static_for<R>([&](auto r) { uh[r] = valid ? ld(U + (t + r * T) * W) : cpx{0.f, 0.f}; });
   __syncthreads();
+  // Every work item of a strip transforms it again: extra work, but no launch and no trip through
+  // memory between the two, which is what a launch of few blocks waits for.
+  if (p.fwd) fft_run<N, R, G::RM, false, SYNC_BLOCK, ColAddr<W, R>, 2>(uh, A, t, ctw);
   const PsiBuf PB(p);
   float ps[R];
   if constexpr (G::PREFETCH) PB.load<N, R, T>(stg.win[0][c], t, ps);

@@ -174,10 +174,21 @@ static __global__ __launch_bounds__(256) void k_epilogue(const float* __restrict
 }
 
 // ---------------------------------------------------------------- reductions
-// Level 1: block b sums partial rows [b*per, min((b+1)*per, n)) in a fixed order.
-static __global__ __launch_bounds__(256) void k_reduce1(const double* __restrict__ parts, long long n, long long per,
-                                                 double* __restrict__ out) {
+// Sums n partial rows of four in a fixed order, in one launch: block b sums rows [b*per,
+// min((b+1)*per, n)) and leaves its sums in red; the block that finishes last (counted in
+// *done, which it sets back to zero) adds the blocks' sums in block order and writes
+// totals[0..3], the history row (r_primal, r_dual, r_combined, surrogate energy) and a
+// non-finite flag in totals[4].  With hist_ctr the row is hist_row + 4 * (*hist_ctr) and the
+// counter advances by one, so one launch sequence (a captured graph) serves every iteration of
+// a solve.  The sums travel between blocks by agent-scope atomics: blocks run on different
+// XCDs, whose L2 caches are not coherent with each other.  A launch of few bytes is all
+// latency: 3.2 + 2.6 us (128^2) and 4.8 + 4.7 us (1024^2, q = 5) as two launches, 3.4 and 8.6 us as
+// one.
+static __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ parts, long long n, long long per,
+                                                       double* red_out, unsigned* done, double* __restrict__ totals,
+                                                       double* __restrict__ hist_row, double gamma, int* hist_ctr) {
   __shared__ double red[4 * 4];
+  __shared__ int last;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   const long long b0 = blockIdx.x * per, b1 = min(b0 + per, n);
   for (long long r = b0 + threadIdx.x; r < b1; r += 256) {
@@ -185,25 +196,24 @@ static __global__ __launch_bounds__(256) void k_reduce1(const double* __restrict
     for (int i = 0; i < 4; ++i) acc[i] += parts[r * 4 + i];
   }
   block_sum4<4>(acc, red);
-  if (threadIdx.x == 0) {
+  if (gridDim.x > 1) {
+    if (threadIdx.x == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) out[blockIdx.x * 4 + i] = acc[i];
-  }
-}
-
-// Level 2: one block; writes totals[0..3], the history row (r_primal, r_dual, r_combined,
-// surrogate energy) and a non-finite flag in totals[4].  With hist_ctr the row is
-// hist_row + 4 * (*hist_ctr) and the counter advances by one, so one launch sequence (a
-// captured graph) serves every iteration of a solve.
-static __global__ __launch_bounds__(256) void k_reduce2(const double* __restrict__ in, int n, double* __restrict__ totals,
-                                                 double* __restrict__ hist_row, double gamma, int* hist_ctr) {
-  __shared__ double red[4 * 4];
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int r = threadIdx.x; r < n; r += 256) {
+      for (int i = 0; i < 4; ++i)
+        __hip_atomic_store(red_out + blockIdx.x * 4 + i, acc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += in[r * 4 + i];
+    for (int i = 0; i < 4; ++i) {
+      acc[i] = threadIdx.x < gridDim.x
+                   ? __hip_atomic_load(red_out + threadIdx.x * 4 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                   : 0.0;
+    }
+    block_sum4<4>(acc, red);
+    if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  block_sum4<4>(acc, red);
   if (threadIdx.x == 0) {
     const double dy2 = acc[SLOT_DY2], db2 = acc[SLOT_DB2];
     totals[0] = acc[0]; totals[1] = acc[1]; totals[2] = acc[2]; totals[3] = acc[3];

@@ -203,6 +203,7 @@ void fill_stage_tables(int n, std::vector<float2>& tw) {
 template <int N> struct WOf { static constexpr int value = ColGeom<N>::W; };
 
 constexpr int kRed1Blocks = 256;
+constexpr int kDoneSlot = 7;   // entry of sdev that holds a reduction's count of blocks done
 constexpr int kDotBlocks = 1024;
 
 struct Layout {
@@ -232,7 +233,7 @@ Layout make_layout(const shs_plan* p) {
   L.nparts = L.nrow_parts + std::max<long long>(2 * npix, kDotBlocks);
   L.parts = off; off = align256(off + size_t(L.nparts) * 4 * 8);
   L.red1 = off;  off = align256(off + kRed1Blocks * 4 * 8);
-  L.sdev = off;  off = align256(off + 8 * 8);   // totals [0, 5), history row counter at [6]
+  L.sdev = off;  off = align256(off + 8 * 8);   // totals [0, 5), counters: history row [6], blocks done [7]
   L.hctr = L.sdev + 6 * 8;
   L.total = off;
   return L;
@@ -426,8 +427,16 @@ void enqueue_synthesis_cols(const Ctx& c, int count) {
   ColParams cp = col_params(c, count);
   cp.in = c.at<float2>(c.L.v);
   cp.out = c.at<float2>(c.L.v);          // column FFT in place: V -> U
-  rec_step(BS_FWD);
-  run_col(c, COL_FWD, cp, p->NS, count);
+  // A synthesis launch that does not fill the GPU (four blocks of four waves per CU) transforms
+  // the columns itself: 128^2, q = 3 (132 blocks) 4.2 + 4.5 -> 5.7 us.  At 512^2, q = 4 (2,024
+  // blocks) both forms take 27 us, at 1024^2, q = 5 (2,795) the separate launch 128 and this
+  // 129.  Mixed-radix sides keep the separate launch: 30 iterations at 360^2, q = 2 took 3.07 ms
+  // with it and 3.18 with the transform inside (a longer chain per block, a strip more of LDS).
+  cp.fwd = !p->generic && (long long)p->n_syn * count <= 1024 ? 1 : 0;
+  if (!cp.fwd) {
+    rec_step(BS_FWD);
+    run_col(c, COL_FWD, cp, p->NS, count);
+  }
   cp.in = c.at<float2>(c.L.v);
   cp.out = c.at<float2>(c.L.t1);
   cp.items = p->items_syn;
@@ -480,12 +489,26 @@ void enqueue_analysis(const Ctx& c, int count) {
   if (p->n_part > 0) run_col(c, COL_FINAL, cp, p->NS, count);
 }
 
+// Sums nparts partial rows: one block up to eight rows per thread (no second step), else blocks of
+// 256 rows or more.
+void launch_reduce(hipStream_t s, const double* parts, long long nparts, double* red, double* sdev, double* hist_row,
+                   double gamma, int* hist_ctr) {
+  const int blocks = nparts <= 2048 ? 1 : int(std::min<long long>(kRed1Blocks, (nparts + 255) / 256));
+  hipLaunchKernelGGL(k_reduce, dim3(blocks), dim3(256), 0, s, parts, nparts, (nparts + blocks - 1) / blocks, red,
+                     reinterpret_cast<unsigned*>(sdev + kDoneSlot), sdev, hist_row, gamma, hist_ctr);
+}
+// Zeroes the workspace's two counters (history row, blocks done of a reduction): before the
+// first launch of a call that reduces.
+void enqueue_zero_counters(const Ctx& c) {
+  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, c.s, reinterpret_cast<uint32_t*>(c.at<double>(c.L.hctr)), 4LL, 0u);
+}
+
 // hist_ctr: NULL (hist_row is the row itself) or the device row counter (hist_row is the
 // history's first row).
 void enqueue_reduce(const Ctx& c, long long nparts, double* hist_row, double gamma, int* hist_ctr = nullptr) {
   if (g_rec) {
     rec_step(BS_REDUCE);
-    LaunchRec& r = rec_add(RK_REDUCE, &k_reduce2, 256, 1, 1, 0);
+    LaunchRec& r = rec_add(RK_REDUCE, &k_reduce, 256, 1, 1, 0);
     r.parts = c.at<double>(c.L.parts);
     r.nparts = nparts;
     r.red1 = c.at<double>(c.L.red1);
@@ -494,11 +517,8 @@ void enqueue_reduce(const Ctx& c, long long nparts, double* hist_row, double gam
     return;
   }
   Timed tm(c.s, KC_REDUCE);
-  const long long per = (nparts + kRed1Blocks - 1) / kRed1Blocks;
-  hipLaunchKernelGGL(k_reduce1, dim3(kRed1Blocks), dim3(256), 0, c.s, c.at<double>(c.L.parts), nparts,
-                     std::max<long long>(per, 1), c.at<double>(c.L.red1));
-  hipLaunchKernelGGL(k_reduce2, dim3(1), dim3(256), 0, c.s, c.at<double>(c.L.red1), kRed1Blocks,
-                     c.at<double>(c.L.sdev), hist_row, gamma, hist_ctr);
+  launch_reduce(c.s, c.at<double>(c.L.parts), nparts, c.at<double>(c.L.red1), c.at<double>(c.L.sdev), hist_row, gamma,
+                hist_ctr);
 }
 
 // Per-filter weights and thresholds from a host Lambda (J+1 per-scale or eta per-filter).
@@ -963,10 +983,7 @@ void launch_batch_iter(const BatchIter& iter, char* dbase, hipStream_t s) {
       (void)hipLaunchKernel(it.fn, dim3(it.blocks), dim3(it.threads), args, it.lds, s);
     } else {
       const LaunchRec& r = it.red;
-      const long long per = std::max<long long>((r.nparts + kRed1Blocks - 1) / kRed1Blocks, 1);
-      hipLaunchKernelGGL(k_reduce1, dim3(kRed1Blocks), dim3(256), 0, s, r.parts, r.nparts, per, r.red1);
-      hipLaunchKernelGGL(k_reduce2, dim3(1), dim3(256), 0, s, r.red1, kRed1Blocks, r.sdev, nullptr, r.gamma,
-                         nullptr);
+      launch_reduce(s, r.parts, r.nparts, r.red1, r.sdev, nullptr, r.gamma, nullptr);
     }
   }
 }
@@ -1559,6 +1576,7 @@ shs_status shs_solve_pd(const shs_plan* p, const shs_pd_params* prm, const float
   // the first iteration
   enqueue_zero(c, c.L.w, size_t(p->q) * n2 * 4);
   enqueue_zero(c, c.L.v, size_t(p->q) * p->n * p->P * 8);
+  enqueue_zero_counters(c);
   LAUNCHCHK("initial state");
   double tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   bool have = false;
@@ -1611,6 +1629,7 @@ shs_status shs_solve_tv(const shs_plan* p, const shs_params* prm, const float* d
   const long long n2 = (long long)p->n * p->n;
   // the first iteration reads no state
   if (prm->iters == 0) enqueue_zero_state(c);
+  enqueue_zero_counters(c);
   LAUNCHCHK("initial state");
   const double rnorm = std::sqrt(double(p->q) * double(n2));
   double tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -1716,6 +1735,7 @@ shs_status shs_solve_nl(const shs_plan* p, const shs_nl_params* prm, const float
   np.tau = prm->tau;
   np.sigma = prm->sigma;
   if (prm->iters > 0) nl_launch(p->store, NL_INDEX, np, c.s);
+  enqueue_zero_counters(c);
   LAUNCHCHK("initial state");
   double tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   bool have = false;
@@ -1872,6 +1892,7 @@ shs_status shs_energy(const shs_plan* p, const shs_params* prm, const float* d_s
   if (!(tmp.gamma > 0.f)) tmp.gamma = 1.f;
   st = set_lambda(c, &tmp);
   if (st != SHS_OK) return st;
+  enqueue_zero_counters(c);
   return energy_of(c, d_u, d_s, h_energy);
 }
 
@@ -1915,7 +1936,7 @@ shs_status solve_impl(const shs_plan* p, const shs_params* prm, const float* d_s
   // History rows are addressed through a device counter (reset here), so the launches of
   // every steady-state iteration are identical.
   int* hctr = d_hist ? c.at<int>(c.L.hctr) : nullptr;
-  if (hctr) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, c.s, reinterpret_cast<uint32_t*>(hctr), 1LL, 0u);
+  enqueue_zero_counters(c);
   // FP16 state overflows to inf beyond 65504: the last iteration's non-finite flag is
   // always reduced and checked for it (one synchronisation), also without h_stats.
   const bool f16_guard = p->store == SHS_STORE_F16;
@@ -2153,6 +2174,7 @@ shs_status shs_solve_batch(shs_batch* b, const shs_params* params, const float* 
         for (int i : b->lanes[l]) {
           ctx[i].s = ls;
           if (iters == 0) enqueue_zero_state(ctx[i]);
+          enqueue_zero_counters(ctx[i]);
         }
         if (iters >= 1) launch_batch_iter(its[l][0], dbase, ls);
         for (int it = 1; it + 1 < iters; ++it) launch_batch_iter(its[l][1], dbase, ls);
