@@ -121,7 +121,10 @@ struct Ops {
   // middle step (MID_*) and its blocks
   void (*mid)(const shs_plan*, int, const MidParams&, hipStream_t);
   int (*mid_blocks)(const shs_plan*);
-  bool (*reserve)();   // dynamic LDS beyond the default limit; false if the runtime refuses
+  // Lets the path's kernels take dynamic LDS beyond the runtime's default limit, where the plan
+  // can need it (as much as the largest plan of the path needs: plans are created in any
+  // order); false if the runtime refuses.
+  bool (*reserve)(const shs_plan*);
 };
 enum { COL_FWD = 0, COL_SYN = 1, COL_ANA = 2, COL_FINAL = 3 };
 
@@ -135,6 +138,7 @@ extern template Ops pow2_ops<1024>();
 extern template Ops pow2_ops<2048>();
 Ops mixed_ops();
 
+constexpr size_t kDefaultDynamicLds = 64 * 1024;
 constexpr int kGenericMaxN = 1024;          // largest image side of the mixed-radix path
 constexpr size_t kRowGLdsMax = 64 * 1024;   // dynamic LDS a generic row block may take
 

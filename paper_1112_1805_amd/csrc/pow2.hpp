@@ -90,7 +90,8 @@ struct MidPipe {
     if (mode == MID_PD) mp.stats ? launch<MID_PD, true>(p, mp, s) : launch<MID_PD, false>(p, mp, s);
     else mp.stats ? launch<MID_ADMM, true>(p, mp, s) : launch<MID_ADMM, false>(p, mp, s);
   }
-  static bool reserve() {
+  static bool reserve(const shs_plan* p) {
+    if (MidGeom<N>::lds(p->q) <= kDefaultDynamicLds) return true;
     const auto one = [](auto fn) {
       return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  int(MidGeom<N>::lds(SHS_MAX_LABELS))) == hipSuccess;

@@ -174,9 +174,13 @@ std::vector<float2> base_twiddles(int n) {
   }
   return tw;
 }
+// float2 entries of the stage lists, and of all that follows a mixed-radix plan's base table.
+constexpr size_t kPlansLen = (3 * sizeof(FftPlan) + sizeof(float2) - 1) / sizeof(float2);
+size_t tables_g_len(int n) { return size_t(n) / 2 * 3 + n + kPlansLen; }
 // The tables of a mixed-radix plan behind its base table: what a row pass copies
 // (exp(-2 pi i k / N) for k <= M = N/2, the inverse and the forward transform's stage tables
-// of M - 1 entries each, one unused entry), then the columns' stage table (N).
+// of M - 1 entries each, one unused entry), then the columns' stage table (N), then the three
+// stage lists themselves.
 void fill_stage_tables_g(const FftPlan& inv, const FftPlan& fwd, const FftPlan& col, const std::vector<float2>& tw,
                          float2* out) {
   const int n = col.L;
@@ -189,6 +193,8 @@ void fill_stage_tables_g(const FftPlan& inv, const FftPlan& fwd, const FftPlan& 
   std::copy(tab.begin(), tab.begin() + M - 1, out + 2 * M);
   out[3 * M - 1] = tw[0];
   fill_stage_tw_g(col, tw, n, out + 3 * M);
+  const FftPlan plans[3] = {inv, fwd, col};
+  std::memcpy(out + 3 * M + n, plans, sizeof(plans));
 }
 void fill_stage_tables(int n, std::vector<float2>& tw) {
   switch (n) {
@@ -576,8 +582,8 @@ shs_status energy_of(const Ctx& c, const float* d_u, const float* d_s, double* o
 void free_plan(shs_plan* p) {
   if (!p) return;
   delete p->graphs;
-  void* bufs[] = {p->psi, p->tw, p->fft, p->eig, p->psiw, p->pwin, p->tcol, p->items_syn, p->items_ana, p->fwin,
-                  p->fgeo, p->strips_ana};
+  void* bufs[] = {p->psi, p->tw, p->eig, p->psiw, p->pwin, p->tcol, p->items_syn, p->items_ana, p->fwin,
+                  p->strips_ana};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete p;
@@ -681,16 +687,17 @@ shs_status build_pruned_layout(shs_plan* p, StripLists* keep) {
   if ((st = upload(&p->items_syn, isyn)) != SHS_OK) return st;
   if ((st = upload(&p->items_ana, iana)) != SHS_OK) return st;
   // the work list: every entry's column windows and plane geometry
-  std::vector<int4> fwin(flist.size() * W, make_int4(0, 0, 0, 0)), fgeo(flist.size());
+  const size_t entries = flist.size();
+  std::vector<int4> list(entries * (W + 1), make_int4(0, 0, 0, 0));   // windows, then geometry
   for (int s = 0; s < p->NS; ++s)
     for (size_t k = 0; k < per_strip[s].size(); ++k) {
       const size_t e = size_t(strip_off[s]) + k;
       const int j = per_strip[s][k];
-      fgeo[e] = tcol[j];
-      for (int c = 0; c < W && s * W + c < half; ++c) fwin[e * W + c] = pwin[size_t(j) * half + s * W + c];
+      list[entries * W + e] = tcol[j];
+      for (int c = 0; c < W && s * W + c < half; ++c) list[e * W + c] = pwin[size_t(j) * half + s * W + c];
     }
-  if ((st = upload(&p->fwin, fwin)) != SHS_OK) return st;
-  if ((st = upload(&p->fgeo, fgeo)) != SHS_OK) return st;
+  if ((st = upload(&p->fwin, list)) != SHS_OK) return st;
+  p->fgeo = p->fwin + entries * W;
   if ((st = upload(&p->strips_ana, strips)) != SHS_OK) return st;
   // 4. compact filter values
   if (hipMalloc(&p->psiw, size_t(std::max<long long>(off, 1)) * 4) != hipSuccess) return fail(SHS_E_NOMEM, "psiw");
@@ -1063,11 +1070,9 @@ shs_status apply_schedule(shs_plan* p, const TuneCfg& c, const StripLists& sl) {
     return fail(SHS_E_DEVICE, "bad schedule");
   const int n = p->n;
   const std::vector<float2> tw = base_twiddles(n);
-  std::vector<float2> tabs(size_t(n) / 2 * 3 + n);
+  std::vector<float2> tabs(tables_g_len(n));
   fill_stage_tables_g(pr, pf, pc, tw, tabs.data());
-  const FftPlan plans[3] = {pr, pf, pc};
   HIPCHK(hipMemcpy(p->tw + n, tabs.data(), tabs.size() * sizeof(float2), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(p->fft, plans, sizeof(plans), hipMemcpyHostToDevice));
   p->prow = pr;
   p->pfwd = pf;
   p->pcol = pc;
@@ -1464,7 +1469,7 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
     fill_stage_tables(n, tw);
   } else {
     const std::vector<float2> base = tw;
-    tw.resize(size_t(n) + n / 2 * 3 + n);
+    tw.resize(size_t(n) + tables_g_len(n));
     fill_stage_tables_g(p->prow, p->pfwd, p->pcol, base, tw.data() + n);
   }
   if (hipMalloc(&p->tw, tw.size() * 8) != hipSuccess) { free_plan(p); return fail(SHS_E_NOMEM, "twiddle allocation"); }
@@ -1473,14 +1478,7 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
     const double sn = std::sin(M_PI * double(k) / double(n));
     eig[k] = float(4.0 * sn * sn);
   }
-  if (!pow2) {
-    const FftPlan plans[3] = {p->prow, p->pfwd, p->pcol};
-    if (hipMalloc(&p->fft, sizeof(plans)) != hipSuccess) { free_plan(p); return fail(SHS_E_NOMEM, "stage lists"); }
-    if (hipMemcpy(p->fft, plans, sizeof(plans), hipMemcpyHostToDevice) != hipSuccess) {
-      free_plan(p);
-      return fail(SHS_E_DEVICE, "stage list copy");
-    }
-  }
+  if (!pow2) p->fft = reinterpret_cast<FftPlan*>(p->tw + n + tables_g_len(n) - kPlansLen);
   if (hipMalloc(&p->eig, size_t(n) * 4) != hipSuccess) { free_plan(p); return fail(SHS_E_NOMEM, "eigenvalue table"); }
   if (hipMemcpy(p->eig, eig.data(), size_t(n) * 4, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(p->tw, tw.data(), tw.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
@@ -1495,11 +1493,10 @@ shs_status shs_plan_create(const shs_shape* shape, int device, shs_plan** out) {
     free_plan(p);
     return fail(SHS_E_DEVICE, "filter generation failed");
   }
-  // kernels whose dynamic LDS exceeds the default limit; the cap is set for the largest plan of
-  // the path, so plans can be created in any order
+  // dynamic LDS beyond the runtime's default limit
   {
     Ops ops;
-    if (!get_ops(p, ops) || !ops.reserve()) {
+    if (!get_ops(p, ops) || !ops.reserve(p)) {
       free_plan(p);
       return fail(SHS_E_DEVICE, "cannot reserve LDS for the plan's kernels");
     }
