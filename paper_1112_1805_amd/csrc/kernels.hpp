@@ -374,19 +374,25 @@ __device__ __forceinline__ void row_c2r(cpx (&a)[RowGeom<N>::R], const float2* _
   const PlaneBuf B(X, pitch * N);
   const int ip0 = t - cb, im0 = G::M - t - cb;
   const int op0 = tix<N>(ip0, row), om0 = tix<N>(im0, row);
-  // Chunk r covers k in [r T, r T + T) for every row of the wave; whether it meets the
-  // window (directly or mirrored) is uniform, so chunks outside it are skipped whole.  Bins
-  // of a partly covered chunk outside the plane's columns map below 0 or at or above
-  // pitch * N: their loads are out of range and read zero.  (Issuing every load instead of
-  // branching was measured slower: this pass keeps the vector-memory data path near
-  // saturation.)
+  // Chunk r covers k in [r T, r T + T) for every row of the wave; whether a group of GR chunks
+  // meets the window (directly or mirrored) is uniform, so groups outside it are skipped whole.
+  // Bins of a partly covered group outside the plane's columns map below 0 or at or above
+  // pitch * N: their loads are out of range and read zero.  Groups of four: one branch per chunk
+  // costs more scalar work and moves (denoising, 16 images of 1024^2: 2.32 against 2.27 ms;
+  // solves of 512^2, q = 4 and 2048^2, q = 8: 5.20 against 5.06 and 68.4 against 66.9 ms; of
+  // 1024^2 the same), and no branch at all is slower (this pass keeps the vector-memory data
+  // path near saturation).
+  constexpr int GR = 4, NG = G::R / GR;
+  static_assert(G::R % GR == 0, "whole groups of chunks");
   cpx xp[G::R], xm[G::R];
-  const auto in_p = [&](int k0) { return k0 < cb + pitch && k0 + G::T > cb; };
-  const auto in_m = [&](int k0) { return k0 <= G::M - cb && k0 + G::T > G::M - cb - pitch; };
-  static_for<G::R>([&](auto r) {
-    constexpr int k0 = r * G::T;
-    xp[r] = cpx{0.f, 0.f};
-    if (in_p(k0)) xp[r] = B.load(row_bin<N, 1>(ip0, op0, r, row));
+  const auto in_p = [&](int k0) { return k0 < cb + pitch && k0 + GR * G::T > cb; };
+  const auto in_m = [&](int k0) { return k0 <= G::M - cb && k0 + GR * G::T > G::M - cb - pitch; };
+  static_for<NG>([&](auto g) {
+    if (in_p(g * GR * G::T)) {
+      static_for<GR>([&](auto e) { xp[g * GR + e] = B.load(row_bin<N, 1>(ip0, op0, g * GR + e, row)); });
+    } else {
+      static_for<GR>([&](auto e) { xp[g * GR + e] = cpx{0.f, 0.f}; });
+    }
   });
   // Each bin is loaded once.  The mirrored bins X[M - k] come from the lanes that loaded
   // them, through the LDS crossbar (ds_bpermute) instead of the vector-memory path: for
@@ -396,30 +402,34 @@ __device__ __forceinline__ void row_c2r(cpx (&a)[RowGeom<N>::R], const float2* _
   const int src = (int(threadIdx.x & 63u) - t + ((G::T - t) & (G::T - 1))) << 2;
   cpx xnyq = cpx{0.f, 0.f};
   if (t == 0 && in_m(0)) xnyq = B.load(om0);
-  static_for<G::R>([&](auto r) {
-    constexpr int k0 = r * G::T;
-    constexpr int rs = G::R - 1 - r;
-    xm[r] = cpx{0.f, 0.f};
-    if (in_m(k0)) {
-      cpx v = cpx{__int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(xp[rs].x))),
-                  __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(xp[rs].y)))};
-      if (t == 0) {
-        if constexpr (r == 0) v = xnyq;
-        else v = xp[G::R - r];
-      }
-      xm[r] = v;
+  static_for<NG>([&](auto g) {
+    if (in_m(g * GR * G::T)) {
+      static_for<GR>([&](auto e) {
+        constexpr int r = g * GR + e, rs = G::R - 1 - r;
+        cpx v = cpx{__int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(xp[rs].x))),
+                    __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(xp[rs].y)))};
+        if (t == 0) {
+          if constexpr (r == 0) v = xnyq;
+          else v = xp[G::R - r];
+        }
+        xm[r] = v;
+      });
+    } else {
+      static_for<GR>([&](auto e) { xm[g * GR + e] = cpx{0.f, 0.f}; });
     }
   });
   // z[k] = s + i d W_N^{-k} with s = X[k] + conj(X[M-k]), d = X[k] - conj(X[M-k]): the
-  // product folded into FMAs; chunks with neither bin range in the window are zero.
-  static_for<G::R>([&](auto r) {
-    constexpr int k0 = r * G::T;
-    if (in_p(k0) || in_m(k0)) {
-      const cpx s = xp[r] + conj(xm[r]), d = xp[r] - conj(xm[r]);
-      const cpx w = pre_twiddle<N, r>(twl, t);   // W_N^{k}
-      a[r] = cpx{fmaf(d.x, w.y, fmaf(-d.y, w.x, s.x)), fmaf(d.x, w.x, fmaf(d.y, w.y, s.y))};
+  // product folded into FMAs; groups with neither bin range in the window are zero.
+  static_for<NG>([&](auto g) {
+    if (in_p(g * GR * G::T) || in_m(g * GR * G::T)) {
+      static_for<GR>([&](auto e) {
+        constexpr int r = g * GR + e;
+        const cpx s = xp[r] + conj(xm[r]), d = xp[r] - conj(xm[r]);
+        const cpx w = pre_twiddle<N, r>(twl, t);   // W_N^{k}
+        a[r] = cpx{fmaf(d.x, w.y, fmaf(-d.y, w.x, s.x)), fmaf(d.x, w.x, fmaf(d.y, w.y, s.y))};
+      });
     } else {
-      a[r] = cpx{0.f, 0.f};
+      static_for<GR>([&](auto e) { a[g * GR + e] = cpx{0.f, 0.f}; });
     }
   });
   fft_run<G::M, G::R, G::RM, true, SYNC_WAVE, Addr, 1>(a, A, t, twl + G::TW_PRE);
