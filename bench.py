@@ -582,7 +582,8 @@ def kernel_units(w, iters, eta, store_bytes):
         "row_solve": ("hbm", 2.0 * store_bytes * eta * q * n * n, "GB/s"),
         "col_syn": ("alu", eta * q * half * cfft_col + q * half * cfft_col, "TFLOP/s"),
         "col_ana": ("alu", eta * q * half * cfft_col + q * half * cfft_col, "TFLOP/s"),
-        # u-update, simplex and b_w update: read z, w, b_w, s, write u, w, b_w
+        # adjoint rows, u-update, simplex, b_w update and row transform of u: read Z, w, b_w, s,
+        # write V, w, b_w (Z, V: half spectra, 4 bytes per pixel and label)
         "pixel": ("hbm", 7.0 * 4 * q * n * n, "GB/s"),
         "row_c2r": ("alu", q * n * rfft_row, "TFLOP/s"),
         "row_r2c": ("alu", q * n * rfft_row, "TFLOP/s"),
