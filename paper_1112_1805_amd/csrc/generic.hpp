@@ -324,6 +324,29 @@ __device__ __forceinline__ void real_post(const float2* Y, int M, int lw, int la
 }
 
 template <class Pair, int R> struct StatePairs { Pair v[R]; };
+// Raw buffer view of one channel's state image; with `bytes` = 0 every load reads zero (a state
+// that need not be read).  A branch per load in its place splits the butterfly into blocks that
+// the scheduler cannot move loads between: the largest radices then kept their loaded pairs and
+// the unfinished outputs live together, past the 128 registers of four waves per SIMD (92..108
+// bytes of scratch per lane in the FP32 forms; none like this).  With the analysis pass's like
+// change, per iteration: 768^2, q = 3, FP32 430 -> 413 us, q = 5, FP16 620 -> 586; 184^2, q = 2 73
+// -> 67; sides of small radices within 1.5%.
+template <class S> struct StateBuf {
+  using Pair = typename S::Pair;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ StateBuf(const void* base, int bytes)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), short(0), bytes, 0x00020000)) {}
+  __device__ __forceinline__ Pair load_pair(int pair) const {
+    const unsigned at = unsigned(pair) * unsigned(sizeof(Pair));
+    if constexpr (sizeof(Pair) == 8) {
+      const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0);
+      const unsigned lo = v[0], hi = v[1];
+      return make_float2(__uint_as_float(lo), __uint_as_float(hi));
+    } else {
+      return __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0);
+    }
+  }
+};
 
 template <int MODE, int ST, bool STATS>
 __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& gp, BlockId bid) {
@@ -358,6 +381,8 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
     long long off;
     plane_geom(p.lin, ch % p.lin.nf, cb, pitch, off);
     const PlaneBuf B(p.spec_in + (ch / p.lin.nf) * p.lin.ls + off, pitch * n);
+    const StateBuf<S> G(reinterpret_cast<const typename S::T*>(p.g) + (long long)ch * n * n,
+                        p.fresh ? 0 : n * n * int(sizeof(typename S::T)));
     // first stage (bins outside the plane's columns are out-of-range buffer loads: zero)
     with_radix(gp.inv()->radix[0], [&](auto R) __attribute__((always_inline)) {
       gstage<R, true>(stage_geom(gp.inv(), 0, 1), lw, 64, lane, isw, NoEarly{}, [&](cpx (&a)[R], int bf, int nb, int c) {
@@ -377,11 +402,8 @@ __device__ __forceinline__ void row_g_body(const RowParams& p, const GenParams& 
       constexpr bool EARLY = STATE && R * sizeof(typename S::Pair) <= 64;
       const auto load_state = [&](int bf, int c) {
         StatePairs<typename S::Pair, STATE ? int(R) : 1> e;
-        const typename S::T* g = state(c);
-        static_for<R>([&](auto i) {
-          e.v[i] = typename S::Pair{};
-          if (!p.fresh) e.v[i] = S::load_pair(g + 2 * (bf + i * nb));
-        });
+        const int at = (row0 + c) * M + bf;
+        static_for<R>([&](auto i) { e.v[i] = G.load_pair(at + i * nb); });
         return e;
       };
       const auto early = [&](int bf, int c) {

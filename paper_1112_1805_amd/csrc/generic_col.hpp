@@ -31,6 +31,14 @@ __device__ __forceinline__ PsiVals<R> psi_load_g(const PsiBuf& pb, int4 win, int
   return o;
 }
 
+// Plane geometry of the item's filter i, in scalar registers: the same for the whole block (read
+// from LDS it counts as divergent, and every access through it became a loop over the lanes).
+__device__ __forceinline__ int4 item_geo(const ItemStage<kGW>& stg, int i) {
+  const int4 g = stg.geo[i];
+  return make_int4(__builtin_amdgcn_readfirstlane(g.x), __builtin_amdgcn_readfirstlane(g.y),
+                   __builtin_amdgcn_readfirstlane(g.z), __builtin_amdgcn_readfirstlane(g.w));
+}
+
 // A strip's transform between `load` (first stage: fills the butterfly's inputs) and `done`
 // (last stage: outputs i at positions bf + i nb, with what `early` loaded); b0/b1: the LDS
 // buffers of the stages between (b1 is used by transforms of more than two stages).  Ends
@@ -113,7 +121,7 @@ __device__ __forceinline__ void colg_syn_body(const ColParams& p, const GenParam
   const PsiBuf pb(p);
   __syncthreads();
   for (int i = 0; i < it.z; ++i) {
-    const int4 geo = stg.geo[i];
+    const int4 geo = item_geo(stg, i);
     float2* o = p.out + l * p.tl.ls + geo_off(geo) + (long long)(it.x - geo.x / kGW) * E;
     col_transform_g<true>(gp, lsw, b0, b0 + E, NoEarlyCol{},
       [&](auto& a, int bf, int nb, int c) {
@@ -140,11 +148,13 @@ __device__ __forceinline__ void colg_ana_body(const ColParams& p, const GenParam
   stage_item(p, it, stg, blockDim.x);
   load_table(lsw, col_sw_g(p.tw, n), n - 1);
   const PsiBuf pb(p);
-  __syncthreads();
   // ba: the accumulator; a thread adds to the positions of its own last-stage butterflies, the
-  // same ones for every filter
+  // same ones for every filter (zeroed here: a branch on the first filter at every addition kept
+  // the butterfly's outputs live across blocks, 80..108 bytes of scratch per lane)
+  for (int e = threadIdx.x; e < E; e += blockDim.x) ba[e] = make_float2(0.f, 0.f);
+  __syncthreads();
   for (int i = 0; i < it.z; ++i) {
-    const int4 geo = stg.geo[i];
+    const int4 geo = item_geo(stg, i);
     const float2* in = p.in + l * p.tl.ls + geo_off(geo) + (long long)(it.x - geo.x / kGW) * E;
     col_transform_g<false>(gp, lsw, b0, b0 + E,
       [&](auto R, int bf, int nb, int c) {
@@ -156,7 +166,7 @@ __device__ __forceinline__ void colg_ana_body(const ColParams& p, const GenParam
         constexpr int R = sizeof(a) / sizeof(cpx);
         const auto add = [&](int k, cpx x, float f) {
           float2* o = ba + (bf + k * nb) * kGW + c;
-          const cpx old = i == 0 ? cpx{0.f, 0.f} : ld(o);
+          const cpx old = ld(o);
           st(o, cpx{fmaf(x.x, f, old.x), fmaf(x.y, f, old.y)});
         };
         if constexpr (R <= 16) {

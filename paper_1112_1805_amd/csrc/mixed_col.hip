@@ -26,9 +26,10 @@ static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     [&](auto& a, int bf, int nb, int c, const auto&) {
       constexpr int R = sizeof(a) / sizeof(cpx);
       const float e1 = c < cols ? eig[blockIdx.x * kGW + c] : 0.f;
+      const float scale = c < cols ? p.inv_n2 : 0.f;
       static_for<R>([&](auto k) {
         const int pos = bf + k * nb;
-        st(bz + pos * kGW + c, a[k] * (c < cols ? p.inv_n2 / (1.f + eig[pos] + e1) : 0.f));
+        st(bz + pos * kGW + c, a[k] * (scale / (1.f + eig[pos] + e1)));
       });
     });
   __syncthreads();
