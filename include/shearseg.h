@@ -122,6 +122,8 @@ size_t shs_state_bytes(const shs_plan* plan);
  * the row and column FFTs, and the filters per synthesis work item; the choice is cached per
  * (GPU arch, N, J, q, store) for the process and, if the environment variable
  * SHEARSEG_TUNE_CACHE names a file, there too (SHEARSEG_TUNE=0 keeps the default schedule).
+ * Lines of that file from another version of the library, or that hold a schedule the tuner
+ * could not have chosen, are passed over.
  * The stage order changes the FFT's rounding, so results are reproducible for a given
  * schedule. */
 const char* shs_plan_describe(const shs_plan* plan);

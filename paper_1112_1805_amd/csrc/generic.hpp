@@ -9,23 +9,11 @@
 // (forward; the inverse swaps the signs of the sine terms).
 #pragma once
 #include "kernels.hpp"
+#include "schedule.hpp"
 
 namespace shs {
 
-constexpr int kMaxStages = 10;
-constexpr int kFirstRadix = 32;   // extra radix of a column transform's first stage
-struct FftPlan {
-  int L;                     // transform length
-  int ns;                    // number of stages
-  int radix[kMaxStages];     // product = L
-  // Division by the stage stride Ns_s = radix[0] * ... * radix[s-1] without a divide:
-  // x / Ns_s = (umulhi(x, mag[s]) + x) >> sh[s] for x < 2^21 (constants from the host).
-  unsigned mag[kMaxStages];
-  int sh[kMaxStages];
-};
 using PlanRef = const __attribute__((address_space(4))) FftPlan*;   // in constant memory
-// LDS buffers of one strip a column transform needs between its stages.
-inline int col_bufs(const FftPlan& pl) { return pl.ns > 2 ? 2 : 1; }
 
 // ---------------------------------------------------------------- small DFTs
 template <int P, bool INV>
@@ -100,10 +88,6 @@ __device__ __forceinline__ void dft_any(cpx (&a)[R]) {
   else dft_odd_prime<R, INV>(a);
 }
 
-// The radices a stage can have; with_radix calls f with the radix as a compile-time value.
-#define SHS_RADICES(X)                                                                     \
-  X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17)  \
-  X(18) X(19) X(20) X(22) X(23) X(24)
 template <class F>
 __device__ __forceinline__ void with_radix(int r, F&& f) {
   switch (r) {
@@ -245,8 +229,7 @@ __device__ __forceinline__ const float2* col_sw_g(const float2* tw, int n) { ret
 // loads from global memory would compete with the data for the vector-memory path.
 //   row pass:     exp(-2 pi i k / N) for k <= N/2, then the two stage tables (N/2 - 1 each)
 //   column pass:  the column FFT's stage table (N - 1 entries, padded to N)
-__host__ __device__ constexpr int row_tab_len(int n) { return 3 * (n / 2); }
-__host__ __device__ constexpr int col_tab_len(int n) { return n; }
+// (row_tab_len and col_tab_len entries, schedule.hpp.)
 __device__ __forceinline__ void load_table(float2* dst, const float2* __restrict__ src, int len) {
 #pragma unroll 4
   for (int e = threadIdx.x; e < len; e += blockDim.x) dst[e] = src[e];   // loads of four entries in flight

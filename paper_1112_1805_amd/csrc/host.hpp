@@ -139,20 +139,6 @@ extern template Ops pow2_ops<2048>();
 Ops mixed_ops();
 
 constexpr size_t kDefaultDynamicLds = 64 * 1024;
-constexpr int kGenericMaxN = 1024;          // largest image side of the mixed-radix path
-constexpr size_t kRowGLdsMax = 64 * 1024;   // dynamic LDS a generic row block may take
-
-// LDS buffers a row-pass wave needs for rw rows: one where every stage is a single pass over
-// the wave's 64 lanes (all its reads precede its writes), else two.
-inline int row_g_bufs(const FftPlan& pl, int rw) {
-  int rmin = pl.radix[0];
-  for (int i = 1; i < pl.ns; ++i) rmin = pl.radix[i] < rmin ? pl.radix[i] : rmin;
-  return pl.L / rmin * rw <= 64 ? 1 : 2;
-}
-// Dynamic LDS of a generic row-pass block: the twiddle tables and each wave's buffers.
-inline size_t row_g_lds_bytes(int M, int rw, int wpb, int nbuf) {
-  return (size_t(wpb) * nbuf * M * rw + row_tab_len(2 * M)) * sizeof(float2);
-}
 // Threads of a column-pass block: one per butterfly of the stage with the most of them, in
 // whole waves, up to 256.
 inline int col_g_threads(const FftPlan& pl) {

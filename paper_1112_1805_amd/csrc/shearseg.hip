@@ -245,86 +245,6 @@ Layout make_layout(const shs_plan* p) {
   return L;
 }
 
-// Radices a stage of a mixed-radix transform can have (with_radix in generic.hpp).
-bool radix_ok(int r) {
-#define SHS_CASE(RR) if (r == RR) return true;
-  SHS_RADICES(SHS_CASE)
-#undef SHS_CASE
-  return false;
-}
-
-// Stage lists worth running for length L, best first: fewest stages (each one costs a trip
-// through LDS), then the smallest largest radix (registers, idle lanes); the two best sets
-// of radices, each in both orders.  Column transforms may also start with radix 32
-// (kFirstRadix).  Empty if L has a prime factor above 23.
-std::vector<std::vector<int>> stage_lists(int L, bool column) {
-  struct Set { std::vector<int> r; bool first; };
-  std::vector<Set> sets;
-  std::vector<int> cur;
-  for (int ns = 2; ns <= 5 && sets.empty(); ++ns) {
-    // non-increasing radix lists of ns stages with product L
-    auto rec = [&](auto&& self, int rest, int left, int most, bool first) -> void {
-      if (left == 0) {
-        if (rest == 1) sets.push_back(Set{cur, first});
-        return;
-      }
-      for (int r = most; r >= 2; --r) {
-        if (rest % r != 0 || !radix_ok(r)) continue;
-        cur.push_back(r);
-        self(self, rest / r, left - 1, r, first);
-        cur.pop_back();
-      }
-    };
-    rec(rec, L, ns, 24, false);
-    if (column && L % kFirstRadix == 0 && sets.empty()) {
-      cur.push_back(kFirstRadix);
-      rec(rec, L / kFirstRadix, ns - 1, 24, true);
-      cur.pop_back();
-    }
-  }
-  std::stable_sort(sets.begin(), sets.end(), [](const Set& a, const Set& b) {
-    return *std::max_element(a.r.begin(), a.r.end()) < *std::max_element(b.r.begin(), b.r.end());
-  });
-  if (sets.size() > 2) sets.resize(2);
-  std::vector<std::vector<int>> out;
-  for (const Set& t : sets) {
-    out.push_back(t.r);
-    std::vector<int> rev = t.r;
-    std::reverse(rev.begin() + (t.first ? 1 : 0), rev.end());
-    if (rev != t.r) out.push_back(rev);
-  }
-  return out;
-}
-
-// Plan of the stages `rs` (in this order; their product is L).
-bool fft_plan_from(int L, const std::vector<int>& rs, FftPlan& pl, bool column) {
-  for (size_t i = 0; i < rs.size(); ++i)
-    if (!radix_ok(rs[i]) && !(column && i == 0 && rs[i] == kFirstRadix)) return false;
-  pl = FftPlan{};
-  pl.L = L;
-  long long prod = 1;
-  for (int r : rs) prod *= r;
-  if (rs.size() < 2 || prod != L || int(rs.size()) > kMaxStages) return false;
-  pl.ns = int(rs.size());
-  int ns = 1;
-  for (int i = 0; i < pl.ns; ++i) {
-    pl.radix[i] = rs[i];
-    // x / ns = (umulhi(x, mag) + x) >> sh with sh = ceil(log2 ns), mag = floor(2^32 (2^sh - ns) / ns) + 1;
-    // exact for every ns <= 2048 and x < 2^21 (x < L * strip width here)
-    int sh = 0;
-    while ((1 << sh) < ns) ++sh;
-    pl.sh[i] = sh;
-    pl.mag[i] = ns == 1 ? 0u : unsigned((((unsigned long long)1 << 32) * ((1ull << sh) - ns)) / ns + 1);
-    ns *= rs[i];
-  }
-  return true;
-}
-
-// The row transforms of one stage list: the inverse runs it as it is, the forward reversed.
-bool row_plans_from(int M, const std::vector<int>& rs, FftPlan& inv, FftPlan& fwd) {
-  return fft_plan_from(M, rs, inv, false) && fft_plan_from(M, std::vector<int>(rs.rbegin(), rs.rend()), fwd, false);
-}
-
 bool get_ops_pow2(int n, Ops& o);
 
 bool get_ops(const shs_plan* p, Ops& o) {
@@ -1006,30 +926,9 @@ void launch_batch_iter(const BatchIter& iter, char* dbase, hipStream_t s) {
 // bounds, and are fixed for a given schedule).  The choice is cached per (arch, N, J, q, store) for the process, and in the
 // file named by SHEARSEG_TUNE_CACHE when set (one line per key); SHEARSEG_TUNE=0 keeps the
 // default schedule.
-struct TuneCfg {
-  int rw = 1, wpb = 4, fc_syn = 1;
-  std::vector<int> prow, pcol;
-};
 std::mutex g_tune_mu;
 std::vector<std::pair<std::string, TuneCfg>> g_tune;   // process cache
 bool g_tune_loaded = false;
-
-std::string join_radices(const std::vector<int>& v, char sep) {
-  std::string out;
-  for (size_t i = 0; i < v.size(); ++i) out += (i ? std::string(1, sep) : std::string()) + std::to_string(v[i]);
-  return out;
-}
-std::vector<int> split_radices(const std::string& t) {
-  std::vector<int> v;
-  size_t i = 0;
-  while (i < t.size()) {
-    size_t j = t.find(',', i);
-    if (j == std::string::npos) j = t.size();
-    v.push_back(std::atoi(t.substr(i, j - i).c_str()));
-    i = j + 1;
-  }
-  return v;
-}
 
 void tune_cache_load() {
   if (g_tune_loaded) return;
@@ -1038,16 +937,11 @@ void tune_cache_load() {
   if (!path || !*path) return;
   FILE* f = std::fopen(path, "r");
   if (!f) return;
-  char key[128], prow[128], pcol[128];
-  int rw, wpb, fc;
-  while (std::fscanf(f, "%127s %d %d %d %127s %127s", key, &rw, &wpb, &fc, prow, pcol) == 6) {
+  char line[512];
+  while (std::fgets(line, sizeof(line), f)) {
+    std::string key;
     TuneCfg c;
-    c.rw = rw;
-    c.wpb = wpb;
-    c.fc_syn = fc;
-    c.prow = split_radices(prow);
-    c.pcol = split_radices(pcol);
-    g_tune.emplace_back(key, c);
+    if (parse_schedule_line(line, key, c)) g_tune.emplace_back(key, c);
   }
   std::fclose(f);
 }
@@ -1056,8 +950,7 @@ void tune_cache_store(const std::string& key, const TuneCfg& c) {
   const char* path = std::getenv("SHEARSEG_TUNE_CACHE");
   if (!path || !*path) return;
   if (FILE* f = std::fopen(path, "a")) {
-    std::fprintf(f, "%s %d %d %d %s %s\n", key.c_str(), c.rw, c.wpb, c.fc_syn, join_radices(c.prow, ',').c_str(),
-                 join_radices(c.pcol, ',').c_str());
+    std::fprintf(f, "%s\n", schedule_line(key, c).c_str());
     std::fclose(f);
   }
 }
@@ -1109,8 +1002,8 @@ shs_status tune_schedule(shs_plan* p, const StripLists& sl) {
   const std::vector<std::vector<int>> row_lists = stage_lists(p->M, false), col_lists = stage_lists(p->n, true);
   base.prow = row_lists[0];
   base.pcol = col_lists[0];
-  for (auto& e : g_tune)
-    if (e.first == key) {
+  for (auto& e : g_tune)   // an entry that the tuner could not have chosen is passed over
+    if (e.first == key && schedule_ok(p->n, e.second, kItemMax)) {
       const shs_status st = apply_schedule(p, e.second, sl);
       if (st == SHS_OK)
         std::snprintf(p->schedule, sizeof(p->schedule), "%s: rows/wave %d, waves/block %d, row radices %s, "
@@ -1165,14 +1058,8 @@ shs_status tune_schedule(shs_plan* p, const StripLists& sl) {
   float best_row = 1e30f;
   for (int rw : {1, 2, 4})
    for (int wpb : {4, 2, 1}) {
-    // a block's rows divide N and its LDS stays within the limit; one wave per block only
-    // where four rows per wave would not otherwise fit
-    if (p->n % (rw * wpb) != 0 || (wpb == 1 && rw < 4)) continue;
     for (const auto& ord : row_lists) {
-      FftPlan pr, pf;
-      if (!row_plans_from(p->M, ord, pr, pf) ||
-          row_g_lds_bytes(p->M, rw, wpb, row_g_bufs(pr, rw)) > kRowGLdsMax)
-        continue;
+      if (!row_shape_ok(p->n, rw, wpb, ord)) continue;
       TuneCfg c = best;
       c.rw = rw;
       c.wpb = wpb;
