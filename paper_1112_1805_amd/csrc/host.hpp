@@ -121,9 +121,9 @@ struct Ops {
   // middle step (MID_*) and its blocks
   void (*mid)(const shs_plan*, int, const MidParams&, hipStream_t);
   int (*mid_blocks)(const shs_plan*);
-  // Lets the path's kernels take dynamic LDS beyond the runtime's default limit, where the plan
-  // can need it (as much as the largest plan of the path needs: plans are created in any
-  // order); false if the runtime refuses.
+  // Lets the path's kernels take LDS (static and dynamic together) beyond the runtime's default
+  // limit, where the plan can need it (as much as the largest plan of the path needs: plans are
+  // created in any order); false if the runtime refuses.
   bool (*reserve)(const shs_plan*);
 };
 enum { COL_FWD = 0, COL_SYN = 1, COL_ANA = 2, COL_FINAL = 3 };
@@ -138,7 +138,7 @@ extern template Ops pow2_ops<1024>();
 extern template Ops pow2_ops<2048>();
 Ops mixed_ops();
 
-constexpr size_t kDefaultDynamicLds = 64 * 1024;
+constexpr size_t kDefaultLds = 64 * 1024;   // a block's static and dynamic LDS without a raised limit
 // Threads of a column-pass block: one per butterfly of the stage with the most of them, in
 // whole waves, up to 256.
 inline int col_g_threads(const FftPlan& pl) {

@@ -1031,6 +1031,8 @@ template <int N> struct MidGeom {
     return w;
   }
   static constexpr size_t lds(int q) { return size_t(RB) * q * RowGeom<N>::LROW * sizeof(float2); }
+  // what a block declares beside that: the twiddle table and the sums of up to eight waves
+  static constexpr size_t lds_static = RowGeom<N>::TW_LDS * sizeof(float2) + 8 * 4 * sizeof(double);
 };
 template <int N, int MODE, bool STATS>
 __device__ __forceinline__ void mid_body(const MidParams& p, BlockId bid) {

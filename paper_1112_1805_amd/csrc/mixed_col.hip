@@ -68,10 +68,11 @@ int mixed_mid_blocks(const shs_plan* p);
 bool mixed_mid_reserve();
 
 static bool mixed_reserve(const shs_plan* p) {
-  // three strips and the table; every label's row slots and second buffers (mixed_mid.hip)
-  const size_t col = (3 * size_t(p->n) * kGW + col_tab_len(p->n)) * sizeof(float2);
-  const size_t mid = (size_t(3) + 4 * p->q + 32) * p->M * sizeof(float2);
-  if (col <= kDefaultDynamicLds && mid <= kDefaultDynamicLds) return true;
+  // three strips, the table and a work item's windows; every label's row slots, second buffers
+  // and the waves' sums (mixed_mid.hip)
+  const size_t col = (3 * size_t(p->n) * kGW + col_tab_len(p->n)) * sizeof(float2) + sizeof(ItemStage<kGW>);
+  const size_t mid = (size_t(3) + 4 * p->q + 32) * p->M * sizeof(float2) + 16 * 4 * sizeof(double);
+  if (col <= kDefaultLds && mid <= kDefaultLds) return true;
   const int bytes = (3 * kGenericMaxN * kGW + col_tab_len(kGenericMaxN)) * int(sizeof(float2));
   return mixed_col_reserve<COL_FWD>() && mixed_col_reserve<COL_SYN>() && mixed_col_reserve<COL_ANA>() &&
          mixed_col_reserve<COL_FINAL>() &&

@@ -91,7 +91,7 @@ struct MidPipe {
     else mp.stats ? launch<MID_ADMM, true>(p, mp, s) : launch<MID_ADMM, false>(p, mp, s);
   }
   static bool reserve(const shs_plan* p) {
-    if (MidGeom<N>::lds(p->q) <= kDefaultDynamicLds) return true;
+    if (MidGeom<N>::lds(p->q) + MidGeom<N>::lds_static <= kDefaultLds) return true;
     const auto one = [](auto fn) {
       return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  int(MidGeom<N>::lds(SHS_MAX_LABELS))) == hipSuccess;
