@@ -102,6 +102,14 @@ template <> struct Store<ST_F16> {
   __device__ __forceinline__ static T from_float(float a) { return f_to_f16(a); }
 };
 
+// Two adjacent pixels of an image that the caller passes in: one 8-byte load, but only the four
+// bytes of a float are given as alignment.
+typedef float f32x2_any_t __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ float2 load2_any(const float* p) {
+  const f32x2_any_t v = *reinterpret_cast<const f32x2_any_t*>(p);
+  return make_float2(v[0], v[1]);
+}
+
 // x clipped to [-th, th] (th >= 0): one median-of-three instruction
 __device__ __forceinline__ float clip(float x, float th) { return __builtin_amdgcn_fmed3f(x, -th, th); }
 
@@ -941,7 +949,7 @@ __device__ __forceinline__ void pixel_rows(const MidParams& p, int row0, int row
     const long long o = (long long)(row0 + r) * n + 2 * k;
     float2 wo[Q], bo[Q], sv[Q];
     static_for<Q>([&](auto l) {
-      sv[l] = *reinterpret_cast<const float2*>(p.s + l * p.n2 + o);
+      sv[l] = load2_any(p.s + l * p.n2 + o);
       wo[l] = bo[l] = make_float2(0.f, 0.f);
       if (p.z) {
         wo[l] = *reinterpret_cast<const float2*>(p.w + l * p.n2 + o);

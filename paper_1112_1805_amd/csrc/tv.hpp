@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void k_tv_rhs(TvParams p) {
   const int r = i / n, c = i - r * n;
   if (p.fresh) {
     static_for<Q>([&](auto l) {
-      const float2 s = ld2(p.s + (long long)l * n2 + i);
+      const float2 s = load2_any(p.s + (long long)l * n2 + i);
       st2(p.rhs + (long long)l * n2 + i, -p.gamma * s.x, -p.gamma * s.y);
     });
     return;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void k_tv_rhs(TvParams p) {
     x1[l] = S::load_pair(a + n2 + i);
     xl[l] = a[n2 + il];
     tt[l] = ld2(p.t + (long long)l * n2 + i);
-    sv[l] = ld2(p.s + (long long)l * n2 + i);
+    sv[l] = load2_any(p.s + (long long)l * n2 + i);
   });
   const float2 b = ld2(p.b + i), bu = ld2(p.b + iu);
   const float m0 = 1.f - 2.f * b.x, m1 = 1.f - 2.f * b.y;
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void k_tv_update(TvParams p) {
       uc[l] = ld2(p.u + o + i);
       ud[l] = ld2(p.u + o + id);
       ur[l] = p.u[o + ir];
-      if constexpr (STATS) sv[l] = ld2(p.s + o + i);
+      if constexpr (STATS) sv[l] = load2_any(p.s + o + i);
     });
     float mm0 = 0.f, mm1 = 0.f;
     float w0[Q], w1[Q], g0[Q], g1[Q];
