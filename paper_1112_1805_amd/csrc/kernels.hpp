@@ -375,7 +375,7 @@ __device__ __forceinline__ cpx pre_twiddle(const float2* twl, int t) {
 // Inverse real FFT of a half-spectrum row (unnormalised): X[0..M] -> x[0..N) with
 // point pair (2p, 2p+1) of p = t + r*T in a[r] = (x[2p], x[2p+1]).  The plane holds the
 // columns [cb, cb + pitch); other bins are zero.  twl: the block's LDS twiddle table.
-template <int N, class Addr>
+template <int N, int GRP, class Addr>
 __device__ __forceinline__ void row_c2r(cpx (&a)[RowGeom<N>::R], const float2* __restrict__ X, int row, int cb,
                                         int pitch, const Addr& A, int t, const float2* twl) {
   using G = RowGeom<N>;
@@ -385,12 +385,8 @@ __device__ __forceinline__ void row_c2r(cpx (&a)[RowGeom<N>::R], const float2* _
   // Chunk r covers k in [r T, r T + T) for every row of the wave; whether a group of GR chunks
   // meets the window (directly or mirrored) is uniform, so groups outside it are skipped whole.
   // Bins of a partly covered group outside the plane's columns map below 0 or at or above
-  // pitch * N: their loads are out of range and read zero.  Groups of four: one branch per chunk
-  // costs more scalar work and moves (denoising, 16 images of 1024^2: 2.32 against 2.27 ms;
-  // solves of 512^2, q = 4 and 2048^2, q = 8: 5.20 against 5.06 and 68.4 against 66.9 ms; of
-  // 1024^2 the same), and no branch at all is slower (this pass keeps the vector-memory data
-  // path near saturation).
-  constexpr int GR = 4, NG = G::R / GR;
+  // pitch * N: their loads are out of range and read zero.
+  constexpr int GR = GRP, NG = G::R / GR;
   static_assert(G::R % GR == 0, "whole groups of chunks");
   cpx xp[G::R], xm[G::R];
   const auto in_p = [&](int k0) { return k0 < cb + pitch && k0 + GR * G::T > cb; };
@@ -475,6 +471,14 @@ __device__ __forceinline__ void row_r2c(cpx (&a)[RowGeom<N>::R], float2* __restr
   if (t == 0) B.store(tix<N>(G::M - cb, row), cpx{HALF ? 2.f * (a[0].x - a[0].y) : a[0].x - a[0].y, 0.f});
 }
 
+// Chunks per group of row_c2r.  A branch per chunk costs scalar work and moves, a larger group
+// works on more bins that are zero.  Measured, row pass alone, one / two / four chunks: 512^2
+// q = 4 FP16 with history 54.6 / 53.1 / 52.3 us, 1024^2 q = 5 FP16 544 / 543 / 546, FP32 784 / 785 / 793,
+// primal-dual 536 / 535 / 542, shrinkage 419 / 402 / 397, 2048^2 q = 8 FP16 3,767 / 3,701 / 3,726, q = 4
+// FP32 2,530 / 2,508 / 2,555.  (No branch at all is slower: this pass keeps the vector-memory data
+// path near saturation.)
+template <int N, int MODE> constexpr int row_group() { return N <= 512 || MODE == ROW_SHRINK ? 4 : 2; }
+
 template <int N, int MODE, int ST, bool STATS>
 __device__ __forceinline__ void row_body(const RowParams& p, BlockId bid) {
   using G = RowGeom<N>;
@@ -519,7 +523,7 @@ __device__ __forceinline__ void row_body(const RowParams& p, BlockId bid) {
     const int f = ch % p.lin.nf;
     plane_geom(p.lin, f, cb, pitch, off);
     const float2* X = p.spec_in + (ch / p.lin.nf) * p.lin.ls + off;
-    row_c2r<N>(a, X, row, cb, pitch, A, t, twl);
+    row_c2r<N, row_group<N, MODE>()>(a, X, row, cb, pitch, A, t, twl);
   }
   if constexpr (MODE == ROW_C2R) {
     float* out = p.real_out + ch * p.real_cs + (long long)row * N;
@@ -1063,7 +1067,7 @@ __device__ __forceinline__ void mid_body(const MidParams& p, BlockId bid) {
       if (s < slots) {
         const RowAddr<G::R> A{gsm + s * G::LROW};
         cpx a[G::R];
-        row_c2r<N>(a, p.z + (s / RB) * ls, row0 + s % RB, 0, p.P, A, t, twl);
+        row_c2r<N, 4>(a, p.z + (s / RB) * ls, row0 + s % RB, 0, p.P, A, t, twl);
         fft_sync<SYNC_WAVE>();
         static_for<G::R>([&](auto r) { st(A.template at<G::R>(tq + r * G::RM, tr), a[r]); });
       }
