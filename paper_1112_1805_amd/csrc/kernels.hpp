@@ -737,7 +737,7 @@ __device__ __forceinline__ void col_syn_body(const ColParams& p, BlockId bid) {
   static_for<R>([&](auto r) { uh[r] = valid ? ld(U + (t + r * T) * W) : cpx{0.f, 0.f}; });
   __syncthreads();
   // Every work item of a strip transforms it again: extra work, but no launch and no trip through
-  // memory between the two, which is what a launch of few blocks waits for.
+  // memory between the two, which is what a small launch waits for.
   if (p.fwd) fft_run<N, R, G::RM, false, SYNC_BLOCK, ColAddr<W, R>, 2>(uh, A, t, ctw);
   const PsiBuf PB(p);
   float ps[R];

@@ -353,12 +353,17 @@ void enqueue_synthesis_cols(const Ctx& c, int count) {
   ColParams cp = col_params(c, count);
   cp.in = c.at<float2>(c.L.v);
   cp.out = c.at<float2>(c.L.v);          // column FFT in place: V -> U
-  // A synthesis launch that does not fill the GPU (four blocks of four waves per CU) transforms
-  // the columns itself: 128^2, q = 3 (132 blocks) 4.2 + 4.5 -> 5.7 us.  At 512^2, q = 4 (2,024
-  // blocks) both forms take 27 us, at 1024^2, q = 5 (2,795) the separate launch 128 and this
-  // 129.  Mixed-radix sides keep the separate launch: 30 iterations at 360^2, q = 2 took 3.07 ms
-  // with it and 3.18 with the transform inside (a longer chain per block, a strip more of LDS).
-  cp.fwd = !p->generic && (long long)p->n_syn * count <= 1024 ? 1 : 0;
+  // Small plans: the synthesis transforms its columns itself, which saves a launch where launches
+  // are what is waited for: 128^2, q = 3 (132 blocks) 4.2 + 4.5 -> 5.7 us, one image of 512^2, q = 1
+  // 28.3 -> 25.5 us for the whole forward transform.  The two forms round differently in the last
+  // bit, so the choice is the plan's, not the launch's: an image's coefficients do not depend on how
+  // many images share its launch.  Up to 256^2 this form is never the slower one (q = 8 at 256^2 40.8
+  // against 41.8 us, a batch of 32 images 1,233 against 1,232 us per iteration); larger plans whose
+  // launches fill the GPU (four blocks of four waves per CU) keep the separate launch: at 512^2, q = 4
+  // (2,024 blocks) both forms take 27 us, at 1024^2, q = 5 (2,795) the separate launch 128 and this
+  // 129.  Mixed-radix sides keep it as well: 30 iterations at 360^2, q = 2 took 3.07 ms with it and
+  // 3.18 with the transform inside (a longer chain per block, a strip more of LDS).
+  cp.fwd = !p->generic && (p->n <= 256 || (long long)p->n_syn * p->q <= 1024) ? 1 : 0;
   if (!cp.fwd) {
     rec_step(BS_FWD);
     run_col(c, COL_FWD, cp, p->NS, count);
