@@ -280,10 +280,13 @@ typedef struct {
  * primal-dual iteration (I + D^T D is not diagonal in the DFT): from u = ubar = y = 0,
  *   y = P_ball(y + sigma D ubar) per pixel over labels and blocks (radius lambda),
  *   u' = P_C(u - tau (D^T y + s)),  ubar = 2 u' - u.
- * d_nbr, d_rev: DEVICE int32 [blocks][N][N] (shs_nl_graph's output).  The dual variable
- * (q * blocks images, the plan's storage type) lives in the state part of the workspace,
- * so the plan needs eta >= blocks (J >= 2 for m = 5).  q <= 8.  Outputs, d_hist rows and
- * h_stats as shs_solve_pd (energy = <u^K, s> + lambda NL-TV(u^K)).
+ * d_nbr, d_rev: DEVICE int32 [blocks][N][N] (shs_nl_graph's output).  The plan needs eta >=
+ * blocks (J >= 2 for m = 5; else SHS_E_UNSUPPORTED).  q <= 8.  The dual variable (one record of q
+ * values of the plan's storage type per pixel and block, 16-bit records padded to whole words)
+ * and an index per pixel and block take the place of the solver state in the workspace, or of
+ * the spectra where they do not fit there; SHS_E_UNSUPPORTED if they fit neither (no supported
+ * shape does that).  Outputs, d_hist rows and h_stats as shs_solve_pd (energy = <u^K, s> +
+ * lambda NL-TV(u^K)).
  * Errors: SHS_E_INVALID, SHS_E_UNSUPPORTED, SHS_E_WORKSPACE, SHS_E_DEVICE, SHS_E_NUMERIC. */
 shs_status shs_solve_nl(const shs_plan* plan, const shs_nl_params* params, const float* d_s, const int32_t* d_nbr,
                         const int32_t* d_rev, void* d_ws, size_t ws_bytes, float* d_u, int32_t* d_labels,

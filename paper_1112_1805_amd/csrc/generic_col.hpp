@@ -6,14 +6,17 @@
 // inputs from where they are (global memory, or the strip's spectrum times the filter) and
 // its last stage hands its outputs on (to global memory, or into the accumulator), so LDS
 // holds the data only between stages and a two-stage transform needs one buffer and two
-// barriers.  The block is as wide as the stages have butterflies (col_threads_g): wider
+// barriers.  The block is as wide as the stages have butterflies (col_g_threads): wider
 // blocks would hold LDS for waves that only wait at barriers.
 #pragma once
 #include "mixed.hpp"
 
 namespace shs {
 
-constexpr int kFinalThreads = 512;   // col_final: the summing of the partials wants many threads
+// col_final: the summing of the partials wants many threads.  512 / 256 / 128 per block, per
+// iteration: 360^2, q = 2 alone 102 / 104 / 109 us; in grouped launches 64 images 12.0 / 12.1 / 12.3 ms, 32
+// images of 96..256 1.04 / 1.03 / 1.03, eight of 360^2 460 / 459 / 465 us.
+constexpr int kFinalThreads = 512;
 
 // Filter values psi_j(k0, k1) of one column window at k0 = bf + i nb: every value is one
 // unconditional buffer load, out of range (zero) outside the window, so all are in flight

@@ -1,8 +1,7 @@
 // Grouped launches for batches of images of different sizes and label counts.
 //
-// One ADMM iteration of an image is a fixed sequence of kernels (adjoint column pass, row
-// pass back to real rows, pixel step, forward row and column passes, synthesis column pass,
-// the fused row pass).  In a batch, each step of that sequence is issued once for all
+// One ADMM iteration of an image is a fixed sequence of kernels (adjoint column passes, the
+// middle step, forward and synthesis column passes, the fused row pass).  In a batch, each step of that sequence is issued once for all
 // images whose kernel has the same compile-time configuration: the launch's blocks are the
 // images' grids laid end to end, a table gives every block its image (task), and the task
 // holds that image's parameters.  Every block then runs exactly the code and arithmetic of

@@ -81,7 +81,7 @@ struct LaunchRec {
   ColParams cp{};
   MidParams mp{};
   GenParams gp{};
-  // RK_REDUCE (one image's two-level FP64 reduction)
+  // RK_REDUCE (one image's FP64 reduction)
   double* parts = nullptr;
   long long nparts = 0;
   double* red1 = nullptr;

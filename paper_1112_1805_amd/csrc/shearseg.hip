@@ -420,8 +420,8 @@ void enqueue_analysis(const Ctx& c, int count) {
   if (p->n_part > 0) run_col(c, COL_FINAL, cp, p->NS, count);
 }
 
-// Sums nparts partial rows: one block up to eight rows per thread (no second step), else blocks of
-// 256 rows or more.
+// Sums nparts partial rows: one block up to eight rows per thread (no second step), else a block per
+// 256 rows, at most kRed1Blocks of them.
 void launch_reduce(hipStream_t s, const double* parts, long long nparts, double* red, double* sdev, double* hist_row,
                    double gamma, int* hist_ctr) {
   const int blocks = nparts <= 2048 ? 1 : int(std::min<long long>(kRed1Blocks, (nparts + 255) / 256));
@@ -897,9 +897,13 @@ void build_batch_iter(const std::vector<LaunchRec>& recs, std::vector<char>& are
   }
 }
 
-// Kernel class of an image: the power-of-two side, or for the mixed-radix path the rows per
-// wave of its row pass and the blocks per CU its column passes' LDS allows (a grouped launch
-// takes its largest image's LDS, so only images of one occupancy share a launch).
+// Kernel class of an image: the power-of-two side, or for the mixed-radix path the rows per wave and
+// waves per block of its row pass, its column blocks' width, and the blocks per CU its column
+// passes' LDS allows (a grouped launch takes its largest image's LDS, so only images of one
+// occupancy share a launch).  The middle step of a class is one launch per block size.  Coarser
+// classes (any column width in one launch, four LDS classes: 68 instead of 108 launches per iteration
+// of 64 images) gain nothing on balance, per iteration: 64 images of 96..768 12.0 -> 12.4 ms and 13.5 ->
+// 13.5, 32 of them in FP16 6.99 -> 6.95, 32 of 96..256 1.04 -> 1.02.
 int batch_class(const shs_plan* p) {
   if (!p->generic) return p->n;
   const int bpc = std::min(6, int(160 * 1024 / col_g_lds_bytes(p, 1)));
@@ -928,9 +932,9 @@ void launch_batch_iter(const BatchIter& iter, char* dbase, hipStream_t s) {
 // The row-pass geometry and the synthesis item size leave the solution bit-identical (the
 // residual partial sums are grouped by block, so the histories can differ in the last
 // bits); the stage order changes the FFT's rounding (results stay within the parity
-// bounds, and are fixed for a given schedule).  The choice is cached per (arch, N, J, q, store) for the process, and in the
-// file named by SHEARSEG_TUNE_CACHE when set (one line per key); SHEARSEG_TUNE=0 keeps the
-// default schedule.
+// bounds, and are fixed for a given schedule).  The choice is cached per (arch, N, J, q, store) for
+// the process, and in the file named by SHEARSEG_TUNE_CACHE when set (one line per key, see
+// schedule.hpp); SHEARSEG_TUNE=0 keeps the default schedule.
 std::mutex g_tune_mu;
 std::vector<std::pair<std::string, TuneCfg>> g_tune;   // process cache
 bool g_tune_loaded = false;
